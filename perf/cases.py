@@ -1,0 +1,285 @@
+"""Performance cases of the relay-attention library: the calls a serving program makes, over the
+range of sizes it makes them in.
+
+One pass is one attention layer of one scheduler step, through the public binding:
+
+  decode     one new token per request: relay_attn_decode
+  append     the same with the step's cache write in the call: relay_attn_decode_append
+  grouped    one new token per request, several applications (system prompts) in one batch with
+             their requests in any order: relay_attn_decode_grouped
+  prompt     several new tokens per request: relay_attn_cache_append, then relay_attn_prefill
+  prompts    the same for consecutive request groups with system prompts of their own:
+             relay_attn_cache_append, then relay_attn_prefill_multi
+
+Lengths (context, new tokens, system prompts of the applications) are spread evenly over the
+case's range and dealt to the requests in an order that depends on the seed, so that the work of a
+case does not depend on the seed.  Values are N(0, 1) in bfloat16, as in the tests and the
+benchmark; physical cache blocks are a random permutation of a pool with spare blocks.
+"""
+import math
+import random
+
+import torch
+
+import paper_2402_14808_amd as ra
+
+UNUSED_BLOCK = 0x7FFFFFF0       # block-table slots behind a request's last block: never followed
+
+# What a case holds beside its own entries.
+DEFAULTS = {
+    "kind": "decode", "batch": 1, "q_heads": 32, "kv_heads": 32, "head_dim": 128,
+    "sys_len": 0, "sys_lo": 0,   # applications: system prompts spread over sys_lo .. sys_len
+    "apps": 1,
+    "ctx_lo": 0, "ctx_hi": 0,    # context in front of the step's new tokens
+    "new_lo": 1, "new_hi": 1,    # new tokens per request
+    "block_size": 16,
+    "slack": 0,                  # block-table columns beyond the longest request
+    "bound": "batch",            # max_context_len: the batch's longest, or "table" (left 0: the capacity)
+    "fp32_out": False, "lse": False,
+}
+
+
+def listed():
+    return [
+        # One interactive user of a small deployment: the smallest call, launches and latency.
+        dict(DEFAULTS, name="decode_one", batch=1, kv_heads=8, sys_len=512, ctx_lo=90, ctx_hi=90),
+        # A test- and smoke-sized model with 64-wide heads, ragged short contexts.
+        dict(DEFAULTS, name="decode_small_d64", batch=16, q_heads=16, kv_heads=16, head_dim=64,
+             sys_len=1000, ctx_lo=16, ctx_hi=255),
+        # The common chatbot batch on a 7B model.
+        dict(DEFAULTS, name="decode_7b", batch=32, sys_len=2048, ctx_lo=127, ctx_hi=127),
+        # The benchmark's headline: a 30B model with a 2048-token system prompt.
+        dict(DEFAULTS, name="decode_30b", batch=32, q_heads=52, kv_heads=52, sys_len=2048,
+             ctx_lo=127, ctx_hi=127),
+        # The long end of the benchmark's sweep over system prompts.
+        dict(DEFAULTS, name="decode_30b_long_prompt", batch=32, q_heads=52, kv_heads=52,
+             sys_len=16384, ctx_lo=127, ctx_hi=127),
+        # A wide batch on a grouped-query 8B model.
+        dict(DEFAULTS, name="decode_8b_gqa", batch=128, kv_heads=8, sys_len=8192, ctx_lo=63,
+             ctx_hi=1023),
+        # Long conversations on the same model: a few requests with long, very unequal contexts, the
+        # launch bounded by the table capacity only; fp32 output and log-sum-exp for a further merge.
+        dict(DEFAULTS, name="decode_long_context", batch=12, kv_heads=8, sys_len=777, ctx_lo=1500,
+             ctx_hi=15000, slack=88, bound="table", fp32_out=True, lse=True),
+        # A step in the middle of a generation loop, the new keys/values written by the call.
+        dict(DEFAULTS, name="append_step", kind="append", batch=32, sys_len=1024, ctx_lo=130,
+             ctx_hi=380, slack=4),
+        # Multi-application hosting: four system prompts, requests in arrival order.
+        dict(DEFAULTS, name="grouped_apps", kind="grouped", batch=48, kv_heads=8, apps=4,
+             sys_lo=600, sys_len=4096, ctx_lo=50, ctx_hi=700),
+        # A burst of new conversations on a 13B model behind a long system prompt.
+        dict(DEFAULTS, name="prompt_13b", kind="prompt", batch=16, q_heads=40, kv_heads=40,
+             sys_len=4096, new_lo=64, new_hi=512),
+        # Further turns of running conversations: a few new tokens each over a cached context.
+        dict(DEFAULTS, name="prompt_turns", kind="prompt", batch=8, kv_heads=8, sys_len=1024,
+             ctx_lo=300, ctx_hi=4000, new_lo=9, new_hi=75),
+        # New conversations of three applications at once, 64-wide heads.
+        dict(DEFAULTS, name="prompts_apps_d64", kind="prompts", batch=9, q_heads=32, kv_heads=8,
+             head_dim=64, apps=3, sys_lo=300, sys_len=2000, new_lo=20, new_hi=400),
+    ]
+
+
+# Head layouts met in the tests and the benchmark, and their 64-wide relatives.
+_HEADS = ((32, 32, 128), (32, 8, 128), (40, 40, 128), (52, 52, 128), (28, 4, 128), (8, 8, 128),
+          (16, 16, 64), (32, 8, 64), (4, 4, 64))
+
+
+def draw(rng):
+    """A case of the ranges the listed ones stand for; no larger than the largest of them."""
+    works = [work(c) for c in listed()]
+    most = {k: max(w[k] for w in works) for k in ("bytes", "flops")}
+
+    def log_int(lo, hi):
+        return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+    while True:
+        kind = rng.choice(("decode", "decode", "append", "grouped", "prompt", "prompt", "prompts"))
+        hq, hkv, d = rng.choice(_HEADS)
+        many = kind in ("prompt", "prompts")
+        case = dict(DEFAULTS, kind=kind, q_heads=hq, kv_heads=hkv, head_dim=d,
+                    batch=log_int(1, 32 if many else 256), sys_len=log_int(100, 16384),
+                    block_size=rng.choice((16, 16, 32)), slack=rng.choice((0, 3, 40)),
+                    bound=rng.choice(("batch", "table")), fp32_out=rng.random() < 0.25,
+                    lse=rng.random() < 0.25)
+        if many:
+            case["new_hi"] = log_int(4, 1024)
+            case["new_lo"] = max(1, int(case["new_hi"] * rng.uniform(0.1, 1.0)))
+            case["ctx_hi"] = log_int(16, 8192) if rng.random() < 0.5 else 0
+        else:
+            case["ctx_hi"] = log_int(16, 16384)
+        case["ctx_lo"] = int(case["ctx_hi"] * rng.uniform(0.1, 1.0))
+        if kind in ("grouped", "prompts"):
+            case["apps"] = rng.randint(2, 8)
+            case["batch"] = max(case["batch"], case["apps"])
+            case["sys_lo"] = max(1, int(case["sys_len"] * rng.uniform(0.1, 1.0)))
+        w = work(case)
+        if all(w[k] <= most[k] for k in most):
+            return case
+
+
+def _spread(lo, hi, n):
+    """n whole numbers spread evenly over lo .. hi, the largest of them hi."""
+    return [hi - (hi - lo) * (n - 1 - i) // max(n - 1, 1) for i in range(n)]
+
+
+def _shares(total, parts):
+    """total requests dealt to `parts` applications, no two shares more than one apart."""
+    return [total // parts + (1 if i < total % parts else 0) for i in range(parts)]
+
+
+def _new_and_context(case):
+    """Per request, before the seed's shuffle: new tokens, and context before them."""
+    n = case["batch"]
+    ctx = _spread(case["ctx_lo"], case["ctx_hi"], n)
+    random.Random(n).shuffle(ctx)          # pairs short and long ones; the same for every seed
+    return list(zip(_spread(case["new_lo"], case["new_hi"], n), ctx))
+
+
+def work(case):
+    """Bytes and operations of one pass: q in, out (and log-sum-exp) out, every system prompt's and
+    every context's keys/values once, new keys/values in and into the cache where the call writes
+    them; two products of 2 * head_dim operations per query row and visible position."""
+    c = case
+    hq, hkv, d = c["q_heads"], c["kv_heads"], c["head_dim"]
+    systems = _spread(c["sys_lo"] if c["apps"] > 1 else c["sys_len"], c["sys_len"], c["apps"])
+    requests = _new_and_context(c)
+    tokens = sum(m for m, _ in requests)
+    written = c["kind"] in ("append", "prompt", "prompts")
+    kv_row = 2 * hkv * d * 2
+    rows_read = sum(systems) + sum(ctx for _, ctx in requests)      # cached keys/values
+    rows_read += tokens                                            # the step's own ones
+    nbytes = tokens * hq * d * (2 + (4 if c["fp32_out"] else 2)) + kv_row * rows_read
+    if c["lse"]:
+        nbytes += tokens * hq * 4
+    if written:
+        nbytes += kv_row * tokens
+    pairs, at = 0, 0                       # (query token, visible position) pairs
+    for app, share in enumerate(_shares(c["batch"], c["apps"])):
+        for m, ctx in requests[at:at + share]:
+            pairs += m * (systems[app] + ctx) + m * (m + 1) // 2
+        at += share
+    return {"bytes": nbytes, "flops": 4 * d * hq * pairs}
+
+
+def tolerance(case):
+    """Against the same attention in 64 bits an fp32 result is off by 1.7e-6 .. 2.6e-6 of its norm and a bf16
+    one by 1.65e-3 .. 1.68e-3 (half a unit in its last place); four times that.  Copied rows are byte-exact."""
+    return {"rel": 1e-5} if case["fp32_out"] else {"rel": 6.6e-3}
+
+
+def _normal(gen, *shape):
+    return torch.randn(*shape, generator=gen, device="cuda").to(torch.bfloat16)
+
+
+def _system_cache(gen, s, hkv, d):
+    """A system prompt's keys or values in the layout the library recommends for them."""
+    _, _, nbytes = ra.relay_attn_system_cache_layout(s, hkv, d)
+    view = ra.system_cache_view(torch.zeros(nbytes // 2, dtype=torch.bfloat16, device="cuda"), s, hkv, d)
+    view.copy_(_normal(gen, s, hkv, d))
+    return view
+
+
+def prepare(case, seed):
+    """What the serving program holds before the call: caches, block tables and lengths of the
+    batch, queries (and new keys/values), output buffers, the parameter block and the workspace."""
+    c = case
+    rng = random.Random(seed)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    hq, hkv, d, n, bs = c["q_heads"], c["kv_heads"], c["head_dim"], c["batch"], c["block_size"]
+
+    # The requests of an application keep together here (the work depends on which system prompt
+    # they see) and change places within it.
+    shares = _shares(n, c["apps"])
+    requests, at = _new_and_context(c), 0
+    sys_id, mixed = [], []
+    for app, share in enumerate(shares):
+        part = requests[at:at + share]
+        rng.shuffle(part)
+        mixed += part
+        sys_id += [app] * share
+        at += share
+    requests = mixed
+    if c["kind"] == "grouped":             # requests in arrival order
+        order = list(range(n))
+        rng.shuffle(order)
+        requests = [requests[i] for i in order]
+        sys_id = [sys_id[i] for i in order]
+    new = [m for m, _ in requests]
+    lens = [m + ctx for m, ctx in requests]
+    tokens, longest = sum(new), max(lens)
+
+    blocks = [-(-length // bs) for length in lens]
+    pool = sum(blocks) + sum(blocks) // 10 + 1
+    free = list(range(pool))
+    rng.shuffle(free)
+    tables, at = [], 0
+    width = max(blocks) + c["slack"]
+    for used in blocks:
+        tables.append(free[at:at + used] + [UNUSED_BLOCK] * (width - used))
+        at += used
+    starts = [0]
+    for m in new:
+        starts.append(starts[-1] + m)
+
+    systems = _spread(c["sys_lo"] if c["apps"] > 1 else c["sys_len"], c["sys_len"], c["apps"])
+    k_sys = [_system_cache(gen, s, hkv, d) for s in systems]
+    v_sys = [_system_cache(gen, s, hkv, d) for s in systems]
+    state = {
+        "kind": c["kind"], "tokens": tokens, "max_new": max(new),
+        "q": _normal(gen, tokens, hq, d),
+        "k_sys": k_sys[-1], "v_sys": v_sys[-1],
+        "k_cache": _normal(gen, pool, hkv, bs, d), "v_cache": _normal(gen, pool, hkv, bs, d),
+        "tables": torch.tensor(tables, dtype=torch.int32, device="cuda"),
+        "lens": torch.tensor(lens, dtype=torch.int32, device="cuda"),
+        "starts": torch.tensor(starts, dtype=torch.int32, device="cuda"),
+        "out": torch.empty(tokens, hq, d, device="cuda",
+                           dtype=torch.float32 if c["fp32_out"] else torch.bfloat16),
+        "lse": torch.empty(tokens, hq, device="cuda") if c["lse"] else None,
+    }
+    if c["kind"] in ("append", "prompt", "prompts"):
+        state["k_new"], state["v_new"] = _normal(gen, tokens, hkv, d), _normal(gen, tokens, hkv, d)
+    state["params"] = ra.make_params(
+        state["q"], state["out"], state["k_sys"], state["k_cache"], state["tables"], batch=n,
+        softmax_scale=1.0 / math.sqrt(d), max_context_len=longest if c["bound"] == "batch" else 0)
+    nbytes = ra.relay_attn_workspace_bytes(state["params"], tokens)
+    state["workspace"] = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    if c["kind"] == "grouped":
+        order, counts = ra.relay_attn_group_requests(sys_id, c["apps"])
+        state["sys_id"] = torch.tensor(sys_id, dtype=torch.int32, device="cuda")
+        state["order"] = torch.tensor(order, dtype=torch.int32, device="cuda")
+        state["prefixes"] = list(zip(k_sys, v_sys, counts))
+    if c["kind"] == "prompts":
+        groups, group_tokens, at = [], [], 0
+        for app, share in enumerate(shares):
+            groups.append((k_sys[app], v_sys[app], at, share))
+            group_tokens.append(sum(new[at:at + share]))
+            at += share
+        state["groups"], state["group_tokens"] = groups, group_tokens
+    return state
+
+
+def run(state):
+    """One attention layer of one scheduler step."""
+    s = state
+    p, q, out, lse, ws = s["params"], s["q"], s["out"], s["lse"], s["workspace"]
+    paged = (s["k_cache"], s["v_cache"], s["tables"], s["lens"])
+    kind = s["kind"]
+    if kind == "decode":
+        ra.relay_attn_decode(p, q, s["k_sys"], s["v_sys"], *paged, out, lse, ws)
+        return out, lse
+    if kind == "grouped":
+        ra.relay_attn_decode_grouped(p, s["prefixes"], s["sys_id"], s["order"], q, *paged, out, lse, ws)
+        return out, lse
+    if kind == "append":
+        ra.relay_attn_decode_append(p, q, s["k_new"], s["v_new"], s["k_sys"], s["v_sys"], *paged,
+                                    out, lse, ws)
+        return out, lse, s["k_cache"], s["v_cache"]
+    ra.relay_attn_cache_append(p, s["k_new"], s["v_new"], s["starts"], s["tokens"], *paged)
+    if kind == "prompt":
+        ra.relay_attn_prefill(p, q, s["starts"], s["tokens"], s["max_new"], s["k_sys"], s["v_sys"],
+                              *paged, out, lse, ws)
+    else:
+        ra.relay_attn_prefill_multi(p, s["groups"], s["group_tokens"], q, s["starts"], s["tokens"],
+                                    s["max_new"], *paged, out, lse, ws)
+    return out, lse, s["k_cache"], s["v_cache"]
