@@ -283,3 +283,40 @@ def run(state):
         ra.relay_attn_prefill_multi(p, s["groups"], s["group_tokens"], q, s["starts"], s["tokens"],
                                     s["max_new"], *paged, out, lse, ws)
     return out, lse, s["k_cache"], s["v_cache"]
+
+
+def exact(case, seed):
+    """What run() returns for the inputs of this seed, with the attention in 64 bits."""
+    c, s = case, prepare(case, seed)
+    hq, hkv, d, bs = c["q_heads"], c["kv_heads"], c["head_dim"], c["block_size"]
+    starts, lens, tables = s["starts"].tolist(), s["lens"].tolist(), s["tables"].tolist()
+    if "k_new" in s:                       # the step's own keys/values go to the end of each context
+        for i, length in enumerate(lens):
+            pos = torch.arange(length - (starts[i + 1] - starts[i]), length, device="cuda")
+            blocks = torch.tensor(tables[i], device="cuda")[pos // bs]
+            for cache, fresh in ((s["k_cache"], s["k_new"]), (s["v_cache"], s["v_new"])):
+                cache[blocks, :, pos % bs] = fresh[starts[i]:starts[i + 1]]
+    if c["kind"] == "grouped":
+        system_of = [s["prefixes"][app][:2] for app in s["sys_id"].tolist()]
+    elif c["kind"] == "prompts":
+        system_of = [(k, v) for k, v, _, share in s["groups"] for _ in range(share)]
+    else:
+        system_of = [(s["k_sys"], s["v_sys"])] * len(lens)
+    out = torch.empty(s["tokens"], hq, d, dtype=torch.float64, device="cuda")
+    lse = torch.empty(s["tokens"], hq, dtype=torch.float64, device="cuda")
+    for i, length in enumerate(lens):
+        m, used = starts[i + 1] - starts[i], -(-length // bs)
+        rows = slice(starts[i], starts[i + 1])
+        blocks = torch.tensor(tables[i][:used], device="cuda")
+        keys, values = (torch.cat((shared, cache[blocks].permute(0, 2, 1, 3).reshape(used * bs, hkv, d)[:length]))
+                        for shared, cache in zip(system_of[i], (s["k_cache"], s["v_cache"])))
+        seen = len(keys) - m               # positions that every new token of the request sees
+        hidden = torch.ones(m, len(keys), dtype=torch.bool, device="cuda").triu(seen + 1)
+        for g in range(hkv):
+            heads = slice(g * (hq // hkv), (g + 1) * (hq // hkv))
+            q, k, v = s["q"][rows, heads].double(), keys[:, g].double(), values[:, g].double()
+            scores = (torch.matmul(q, k.t().contiguous()) / math.sqrt(d)).masked_fill_(hidden[:, None], -math.inf)
+            lse[rows, heads] = torch.logsumexp(scores, -1)
+            out[rows, heads] = torch.matmul(torch.softmax(scores, -1), v)
+    caches = (s["k_cache"].double(), s["v_cache"].double()) if "k_new" in s else ()
+    return (out, lse if c["lse"] else None) + caches
