@@ -10,13 +10,20 @@
 
 namespace ra {
 
-template <int D, bool MULTI>
+// P groups of D/4 threads share an output row, group k taking every P-th batch of eight partials, and
+// merge through LDS.  P = 1 where the rows alone fill the machine; with few rows that have many
+// partials each (a few requests with long contexts: 384 rows of up to 40) the batches of one row
+// would otherwise be one trip to memory after the other on a machine that is nearly empty.
+template <int D, bool MULTI, int P>
 __global__ __launch_bounds__(kThreads) void fuse_kernel(const FuseArgs a) {
     constexpr int TPR = D / 4;                  // threads per output row (4 elements each)
-    constexpr int RPB = kThreads / TPR;         // rows per block
-    const int row = blockIdx.x * RPB + threadIdx.x / TPR;
+    constexpr int RPB = kThreads / (TPR * P);   // rows per block
+    static_assert(P == 1 || RPB == 1, "the groups of a row are the whole workgroup");
+    __shared__ int sm_end[2][P];
+    const int part = P == 1 ? 0 : threadIdx.x / TPR;
+    const int row = P == 1 ? blockIdx.x * RPB + threadIdx.x / TPR : blockIdx.x;
     const int e = (threadIdx.x % TPR) * 4;
-    if (row >= a.rows) return;
+    if (row >= a.rows) return;                  // (P > 1: uniform)
 
     // Loads are issued eight partials at a time before any of them is used: the partials were
     // written by other compute units, so each one costs a trip to L2 or memory, and a loop that
@@ -24,58 +31,93 @@ __global__ __launch_bounds__(kThreads) void fuse_kernel(const FuseArgs a) {
     // branches a slot that does not exist is loaded from slot 0 and discarded by a select.
     constexpr int U = 8;
     // With several shared prefixes (App. D) a request whose prefix is shorter than the longest one
-    // has fewer system chunks; the partial slots [skip_lo, skip_hi) of its rows were never written.
-    int skip_lo = 0, skip_hi = 0;
+    // has fewer system chunks; the partial slots [n_sys, n_sys_chunks) of its rows were never
+    // written, and the row's partials are numbered without them.
+    int gap_at = 0, gap = 0;
     if (MULTI) {
         const int token = row / a.Hq;
         int pfx = 0;
         if (a.req_prefix) pfx = a.req_prefix[token];
         else
             while (pfx + 1 < a.n_prefixes && token >= a.pfx_token_end[pfx]) ++pfx;
-        skip_lo = a.pfx_chunks[pfx];
-        skip_hi = a.n_sys_chunks;
+        gap_at = a.pfx_chunks[pfx];
+        gap = a.n_sys_chunks - gap_at;
     }
-    auto present = [&](int p) {
-        return p < a.n_partials && !(MULTI && p >= skip_lo && p < skip_hi);
-    };
+    const int n = a.n_partials - gap;
+    const int64_t oo = (int64_t)(row / a.Hq) * a.o_stride_token + (int64_t)(row % a.Hq) * a.o_stride_head + e;
     // One trip to memory per eight partials: log-sum-exps and payloads are loaded together and
     // merged with a running maximum (the same online rescaling the attention kernels use), rather
     // than reading all log-sum-exps first to find the maximum and then coming back for the rest.
+    // The slots behind an end mark hold anything; they are loaded with their batch and discarded.
+    // (v_exp_f32 as it is: a weight below the normal range cannot reach a sum that holds a 1.)
     float M = -INFINITY, W = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int p0 = 0; p0 < a.n_partials; p0 += U) {
+    int end = INT_MAX;
+    for (int round = 0; round * (P * U) < n; ++round) {
+        const int p0 = round * (P * U) + part * U;
         float l[U];
         f32x4 o[U];
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            const bool ok = present(p0 + j);
-            const int64_t slot = (int64_t)(ok ? p0 + j : 0) * a.rows + row;
+            const bool ok = p0 + j < n;
+            const int p = MULTI && p0 + j >= gap_at ? p0 + j + gap : p0 + j;
+            const int64_t slot = (int64_t)(ok ? p : 0) * a.rows + row;
             l[j] = a.part_lse[slot];
             o[j] = *reinterpret_cast<const f32x4 *>(a.part_o + slot * D + e);
             l[j] = ok ? l[j] : -INFINITY;
         }
+#pragma unroll
+        for (int j = U - 1; j >= 0; --j)
+            if (__float_as_uint(l[j]) == kEndOfPartials) end = p0 + j;
+        if constexpr (P > 1) {                  // the row's end is the first one that any group met
+            if (e == 0) sm_end[round & 1][part] = end;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < P; ++k) end = min(end, sm_end[round & 1][k]);
+        }
         float Mb = M;
 #pragma unroll
-        for (int j = 0; j < U; ++j) Mb = fmaxf(Mb, l[j]);
+        for (int j = 0; j < U; ++j) {
+            l[j] = p0 + j < end ? l[j] : -INFINITY;
+            Mb = fmaxf(Mb, l[j]);
+        }
         const float m_use = finite_or_zero(Mb);
-        const float corr = exp2f(M - m_use);      // M = -inf (nothing yet): 0, and acc, W are 0
+        const float corr = __builtin_amdgcn_exp2f(M - m_use);      // M = -inf (nothing yet): 0, and acc, W are 0
         acc *= corr;
         W *= corr;
         M = Mb;
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            // An empty or absent slot has w = 0; its payload may never have been written (a context
-            // slot an item does not use only gets lse = -inf), so it is dropped by a select.
-            const float w = exp2f(l[j] - m_use);
+            // An empty or absent slot has w = 0; its payload may never have been written, so it is
+            // dropped by a select.
+            const float w = __builtin_amdgcn_exp2f(l[j] - m_use);
             const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
             acc += (w > 0.f ? o[j] : zero) * w;
             W += w;
         }
+        if (end <= (round + 1) * (P * U)) break;
+    }
+    if constexpr (P > 1) {
+        __shared__ f32x4 sm_acc[P][TPR];
+        __shared__ float sm_m[P], sm_w[P];
+        sm_acc[part][e / 4] = acc;
+        if (e == 0) sm_m[part] = M, sm_w[part] = W;
+        __syncthreads();
+        if (part != 0) return;
+#pragma unroll
+        for (int k = 0; k < P; ++k) M = fmaxf(M, sm_m[k]);
+        const float m_use = finite_or_zero(M);
+        W = 0.f;
+        acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            const float f = __builtin_amdgcn_exp2f(sm_m[k] - m_use);
+            acc += sm_acc[k][e / 4] * f;
+            W = fmaf(sm_w[k], f, W);
+        }
     }
     const float inv = W > 0.f ? 1.f / W : 0.f;
     acc *= inv;
-    const int token = row / a.Hq, hq = row % a.Hq;
-    const int64_t oo = (int64_t)token * a.o_stride_token + (int64_t)hq * a.o_stride_head + e;
     if (a.out_is_fp32) {
         *reinterpret_cast<f32x4 *>(static_cast<float *>(a.out) + oo) = acc;
     } else {
@@ -148,25 +190,26 @@ hipError_t launch_cache_append(const AppendArgs &a, hipStream_t stream) {
     return hipGetLastError();
 }
 
+template <int D>
+static void launch_fuse_d(const FuseArgs &a, hipStream_t stream) {
+    constexpr int TPR = D / 4, P = kThreads / TPR;      // split form: one row per workgroup
+    // More than two batches of eight partials and no more rows than the chip holds workgroups of
+    // this kind at once: split (384 rows of up to 40 partials in
+    // 131 slots take 5.2 us; three batches one after the other, 24 slots, took 5.1).
+    const bool split = a.n_partials > 16 && a.rows <= 2048;
+    const bool multi = a.n_prefixes > 1;
+    const dim3 grid(split ? a.rows : (a.rows + P - 1) / P), block(kThreads);
+    if (split && multi) hipLaunchKernelGGL((fuse_kernel<D, true, P>), grid, block, 0, stream, a);
+    else if (split) hipLaunchKernelGGL((fuse_kernel<D, false, P>), grid, block, 0, stream, a);
+    else if (multi) hipLaunchKernelGGL((fuse_kernel<D, true, 1>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((fuse_kernel<D, false, 1>), grid, block, 0, stream, a);
+}
+
 hipError_t launch_fuse(const FuseArgs &a, int head_dim, hipStream_t stream) {
     if (a.rows == 0) return hipSuccess;
-    if (head_dim == 128) {
-        const int rpb = kThreads / 32;
-        const dim3 grid((a.rows + rpb - 1) / rpb);
-        if (a.n_prefixes > 1)
-            hipLaunchKernelGGL((fuse_kernel<128, true>), grid, dim3(kThreads), 0, stream, a);
-        else
-            hipLaunchKernelGGL((fuse_kernel<128, false>), grid, dim3(kThreads), 0, stream, a);
-    } else if (head_dim == 64) {
-        const int rpb = kThreads / 16;
-        const dim3 grid((a.rows + rpb - 1) / rpb);
-        if (a.n_prefixes > 1)
-            hipLaunchKernelGGL((fuse_kernel<64, true>), grid, dim3(kThreads), 0, stream, a);
-        else
-            hipLaunchKernelGGL((fuse_kernel<64, false>), grid, dim3(kThreads), 0, stream, a);
-    } else {
-        return hipErrorInvalidValue;
-    }
+    if (head_dim == 128) launch_fuse_d<128>(a, stream);
+    else if (head_dim == 64) launch_fuse_d<64>(a, stream);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

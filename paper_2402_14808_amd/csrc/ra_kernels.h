@@ -10,6 +10,11 @@ namespace ra {
 // r = token * Hq + head, part_o[(p * rows + r) * D + e] is the normalised partial
 // attention output (fp32) and part_lse[p * rows + r] its log-sum-exp in the base-2
 // domain (log2 of the sum of 2^(logit * scale * log2 e)); -inf marks an empty partial.
+// A row takes its context slots from the first one on; where it leaves some unused, the log-sum-exp
+// of the first unused one is kEndOfPartials and the ones behind it are never written.  (A number
+// that is not one and that no computation on bf16 data produces: the hardware's own has a zero low
+// half, and so has one that came in with the data.)
+constexpr uint32_t kEndOfPartials = 0x7fedcba9u;
 
 struct CtxArgs {                 // per-request paged decode attention, item = (request, kv head, part)
     const uint16_t *q, *k_cache, *v_cache;

@@ -280,17 +280,20 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
                 // t_est: tiles per wavefront if every context had the maximum length.  Real
                 // lengths are shorter and the spans shrink with them, down to the floor below; a
                 // floor near t_est would leave most context wavefronts without work (a batch
-                // with lengths uniform in [64, 1024] has half the tiles the plan assumed).  So the
-                // floor is a quarter of t_est, as far as the partials of a row (system chunks +
-                // context slots) do not start another pass of the fusion kernel, which reads
-                // them eight at a time.
+                // with lengths uniform in [64, 1024] has half the tiles the plan assumed; one of
+                // 1500 .. 15000 under a bound of 16400 has half of them as well).  So the floor is
+                // an eighth of t_est.  Slots that the real lengths do not need cost workspace only
+                // (the fusion reads the ones that were written); the partials stay within the
+                // static scratch unless even a floor of t_est itself takes more.
+                // (12 requests, 8 kv heads, contexts 1500 .. 15000: 95.9 -> 73.5 us with
+                // spans of 12 tiles on every wavefront instead of 24 on half of them)
                 const int64_t t_est = (ctx_tiles + 4 * wgs - 1) / (4 * wgs);
                 int64_t slots = (t_max + t_est - 1) / t_est + 1;
-                int64_t t_low = (t_est + 3) / 4;
+                int64_t t_low = (t_est + 7) / 8;
                 if (t_low < kMinWaveTiles) t_low = kMinWaveTiles < t_est ? kMinWaveTiles : t_est;
                 int64_t wide = (t_max + t_low - 1) / t_low + 1;
-                const int64_t filled = pl.n_sys_chunks + slots;
-                const int64_t room = (filled <= 6 ? 8 : filled <= 14 ? 16 : 24) - pl.n_sys_chunks;
+                const int64_t room = (int64_t)((kStaticScratchBytes - 512) / ((size_t)pl.rows * (d * 4 + 4))) -
+                                     pl.n_sys_chunks;
                 if (wide > room) wide = room;
                 if (wide > slots) slots = wide;
                 pl.n_ctx_parts = (int)slots;

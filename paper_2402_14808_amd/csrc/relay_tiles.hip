@@ -474,7 +474,7 @@ __device__ __forceinline__ int wave_inclusive_scan(int x, int lane) {
 // computed from the context lengths found on the device, so the split is even however the
 // lengths are distributed.  A span that crosses from one (request, kv head) item into the next is
 // processed as one segment per item; segment number k of an item writes context partial slot k,
-// and the wavefront that begins an item marks the slots the item does not use as empty.  The
+// and the wavefront that ends an item marks the slot behind it (kEndOfPartials).  The
 // host chose ctx_t_floor so that no item has more than n_ctx_slots segments.  An empty context
 // counts as one tile without keys, so that its rows still get their (empty) partial.
 //
@@ -616,19 +616,18 @@ __device__ __forceinline__ void run_context_wave(const TileArgs &a, unsigned cha
         // span can continue an item, so the walk starts at this wavefront's own first tile)
         int slot = 0;
         for (uint32_t pos = x0; pos > item_first; ++slot) pos -= len_of_wave(uw - 1 - (uint32_t)slot);
-        // The lane id goes through an opaque move so that the per-lane address terms of the slot
-        // marking and of the tile pipeline are recomputed for every segment instead of being kept
+        // The lane id goes through an opaque move so that the per-lane address terms of the tile
+        // pipeline are recomputed for every segment instead of being kept
         // live across this loop, where they would not fit the register file.
         int lane_here = lane;
         asm volatile("" : "+v"(lane_here));
-        if (j == 0) {                             // this wavefront begins the item
-            // spans the item touches: this one and every later one that begins inside the item
-            int n_seg = 1;
-            for (uint32_t pos = x0 + my_len; pos < item_first + T; ++n_seg) pos += len_of_wave(uw + (uint32_t)n_seg);
-            if (lane_here < a.G)
-                for (int sl = n_seg; sl < a.n_ctx_slots; ++sl)
-                    a.part_lse[(int64_t)(a.n_sys_chunks + sl) * a.rows + (int64_t)req * a.Hq +
-                               g * a.G + lane_here] = -INFINITY;
+        // the wavefront that ends the item knows how many slots it has taken
+        // (the address is computed per lane: scalar registers are what this function runs short of)
+        if (j + seg == T && slot + 1 < a.n_ctx_slots && lane_here < a.G) {
+            const int row = req * a.Hq + (g * a.G + lane_here);
+            int next = a.n_sys_chunks + slot + 1;
+            asm volatile("" : "+v"(next));
+            a.part_lse[(int64_t)next * a.rows + row] = __uint_as_float(kEndOfPartials);
         }
         Item it;
         it.g = g;
