@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <mutex>
 
 #include "ra_kernels.h"
@@ -32,6 +33,7 @@ struct Plan {
     int ctx_wgs;          // decode: context workgroups (four wavefronts each) in the tile launch
     int ctx_t_floor;      // decode: least tiles per context wavefront, bounds the slots per row
     bool paired;          // decode: the launch is exactly two workgroups per compute unit
+    bool whole;           // prompt phase: one launch of items that write the output themselves
     bool unsupported;
     int max_ctx;
     int block_size_log2;
@@ -114,6 +116,83 @@ ra_status static_scratch(void **ptr) {
     }
     *ptr = known[dev];
     return RA_OK;
+}
+
+// The longest context part whose block ids fit an item's table in LDS.
+int longest_part(const ra_params *p) {
+    int64_t cap = (int64_t)ra::kMaxPartBlocks * p->block_size;
+    if (cap > 4096) cap = 4096;
+    const int part = (int)(cap / 128 * 128);
+    return part < 128 ? 128 : part;
+}
+
+// How the prompt phase is cut, where the caller leaves it to the library.
+struct PromptSplit {
+    bool whole;          // one launch of items that go through prompt and contexts (see `run`)
+    int chunk, part;     // otherwise: system positions and context positions of an item
+};
+
+// A prompt-phase launch takes about as long as the larger of its longest item and its work per
+// compute unit, plus the thin end of the launch; a finer cut shortens the first and the last
+// of these and costs partials, which are written, read again and fused.  The estimate below was
+// fitted to 570 measured cuts of 16 shapes (system prompts of 300 .. 12000, contexts up to 8000, 80 ..
+// 14400 stacked rows per kv head, 4 .. 40 kv heads, head_dim 64 and 128): its choice took within 3 % of the
+// best cut of each shape on most and 13 % at worst, against up to 3.5 times for the fixed rule in front of it
+// (chunks of 512 or more, one context part of 4096 positions): 8 requests of 9 .. 75 tokens behind
+// contexts of 300 .. 4000 118 -> 75 us, 4 requests of 10 .. 100 tokens behind 500 .. 2000 132 -> 38 us.
+// Uses nothing that the workspace size is not computed from.
+PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx) {
+    const int64_t G = p->num_q_heads / p->num_kv_heads, hkv = p->num_kv_heads, batch = p->batch > 0 ? p->batch : 1;
+    const int64_t s = p->sys_len, base = hkv * ((total_q * G + 127) / 128);
+    const double row_bytes = (double)total_q * p->num_q_heads * p->head_dim * 4;
+    const double step_us = p->head_dim == 128 ? 1.5 : 1.1;     // 64 keys by 128 rows, a compute unit to itself
+    const double cus = device_compute_units();
+    const double mean_new = (double)total_q / batch, ctx = 0.85 * max_ctx;      // (lengths live on the device)
+    // items per context part: blocks of 128 stacked rows of an average request, times kv heads and requests
+    const int64_t ctx_base = batch * hkv * (((total_q + batch - 1) / batch * G + 127) / 128);
+    const double steps = ((double)base * s + ctx_base * ctx) / 64;
+    auto launch_us = [&](double longest, double all, double items) {
+        const double even = all / cus + 0.35 * longest;
+        return step_us * (longest > even ? longest : even) + 2.0 * items / cus;
+    };
+    PromptSplit best{false, 128, longest_part(p)};
+    double best_us = 1e300;
+    const int longest = best.part;
+    const int64_t most_chunks = s > 0 ? (s + 127) / 128 : 1;
+    const int64_t most_parts = max_ctx > 0 ? (max_ctx + 127) / 128 : 1;
+    const int64_t least_parts = max_ctx > 0 ? (max_ctx + longest - 1) / longest : 1;
+    // (no more items than a launch index holds, whatever the longest request brings)
+    const int64_t rb_most = batch * hkv * ((total_q * G + 127) / 128);
+    for (int64_t nc = 1; nc <= most_chunks; nc += (nc + 1) / 2) {
+        const int64_t chunk = (((s > 0 ? s : 1) + nc - 1) / nc + 127) / 128 * 128;
+        const int64_t n_chunks = (s + chunk - 1) / chunk;
+        for (int64_t np = least_parts; np <= most_parts; np += (np + 1) / 2) {
+            int64_t part = (((max_ctx > 0 ? max_ctx : 1) + np - 1) / np + 127) / 128 * 128;
+            if (part > longest) part = longest;
+            if (np > least_parts && (rb_most * (np + 1) > (1 << 30) || base * n_chunks > (1 << 30))) break;
+            const double parts = max_ctx > 0 ? ceil(ctx / part) : 0;
+            const double t_sys = (double)(chunk < s ? chunk : s) / 64, t_ctx = (double)(part < max_ctx ? part : max_ctx) / 64;
+            const double us = launch_us(t_sys > t_ctx ? t_sys : t_ctx, steps, base * n_chunks + ctx_base * parts) +
+                              row_bytes * (n_chunks + parts) * (2 / 5e6) + 12;
+            if (us < best_us) best_us = us, best.chunk = (int)chunk, best.part = (int)part;
+        }
+    }
+    // Whole items: where blocks of 128 rows alone come near to filling the machine (or the prompt is
+    // too short to be cut) and a block does not meet too many requests: at least 32 new tokens per request, or 4
+    // with a short prompt, where the partials and the fusion launch weigh more than that walk (measured:
+    // 256 requests of 4 .. 12 tokens at s = 512 145 against 162 us, 512 requests of 4 tokens at
+    // s = 1024 80 against 114 us; 128 requests of 16 tokens at s = 4096 328 against 311 us) -- unless
+    // an item's walk of more than 2048 positions is what the launch would wait for (2
+    // requests of 300 .. 1000 tokens behind contexts of 3000 .. 8000: 323 us whole, 216 .. 225 cut).
+    const bool few_blocks = (400 + base / 2) / base > 1 && s > 512;
+    const double met = mean_new > 0 ? 128.0 / G / mean_new + 1 : 1;     // requests with rows in a block
+    const double walk = (double)s + (met < batch ? met : batch) * max_ctx;
+    const double walk_mean = (double)s + (met < batch ? met : batch) * ctx;
+    best.whole = !few_blocks && (total_q >= kWholeMinTokens * batch || (s <= 1024 && total_q >= 4 * batch)) &&
+                 (walk <= 2048 || launch_us(walk / 64, walk_mean / 64 * base, (double)base) <= best_us);
+    if (best.whole) best.chunk = (int)((s + 127) / 128 * 128), best.part = longest;
+    if (best.chunk < 128) best.chunk = 128;
+    return best;
 }
 
 // The least work worth giving a wavefront of the tile launch.
@@ -305,10 +384,14 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
         return pl;
     }
 
+    PromptSplit split{};
+    const bool hand_set = p->sys_chunk_tokens != 0 || p->ctx_part_tokens != 0;
+    if (prefill && !hand_set) split = split_prompt(p, total_q, pl.max_ctx);
+    pl.whole = split.whole;
     if (p->sys_len > 0) {
         int chunk = p->sys_chunk_tokens;
-        if (chunk == 0) {
-            // Many-rows kernel: about 400 workgroups of at least 512 positions (measured).
+        if (chunk == 0 && (hand_set || !prefill)) {
+            // (the other length is set by hand) about 400 workgroups of at least 512 positions
             const int64_t base_items = (int64_t)p->num_kv_heads * pl.n_sys_rowblocks;
             int64_t n_chunks = (400 + base_items / 2) / base_items;
             const int64_t max_chunks = ceil_div(p->sys_len, 512);
@@ -316,21 +399,14 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
             if (n_chunks < 1) n_chunks = 1;
             chunk = ceil_div(ceil_div(p->sys_len, (int)n_chunks), 128) * 128;
         }
+        if (chunk == 0) chunk = split.chunk;
         pl.sys_chunk = chunk;
         pl.n_sys_chunks = ceil_div(p->sys_len, chunk);
     }
     if (pl.max_ctx > 0) {
-        if (p->ctx_part_tokens > 0) {
-            pl.ctx_part = p->ctx_part_tokens;
-        } else if (prefill) {
-            // one part unless the block table of a part would not fit its LDS table
-            int64_t cap = (int64_t)ra::kMaxPartBlocks * p->block_size;
-            if (cap > 4096) cap = 4096;
-            pl.ctx_part = (int)(cap / 128 * 128);
-            if (pl.ctx_part < 128) pl.ctx_part = 128;
-        } else {
-            pl.ctx_part = 256;
-        }
+        if (p->ctx_part_tokens > 0) pl.ctx_part = p->ctx_part_tokens;
+        else if (prefill) pl.ctx_part = hand_set ? longest_part(p) : split.part;
+        else pl.ctx_part = 256;
         pl.n_ctx_parts = ceil_div(pl.max_ctx, pl.ctx_part);
         // a context part may touch at most kMaxPartBlocks blocks (the per-item block-id table in
         // LDS); parts start at multiples of ctx_part, which are block boundaries only when the
@@ -435,21 +511,11 @@ ra_status run(const ra_params *p, const void *q, const int32_t *cu_seqlens_q, in
     const bool prefill = cu_seqlens_q != nullptr;
     const int head_fastest = p->sys_stride_head < p->sys_stride_token ? 1 : 0;
 
-    // Prompt phase in ONE launch: when the system prompt is a single chunk anyway (launches with
-    // many row blocks) and the requests bring many new tokens each, a work item carries its 128
-    // rows through the system prompt and then through the contexts of the requests they belong
-    // to, and writes the output itself; no partials, no fusion launch.  With few tokens per
-    // request a block would walk through many requests' contexts one after the other, so the
-    // split form (context items of their own) stays for those, unless the system prompt is short:
-    // then the partials and the fusion launch of the split form weigh more than that walk
-    // (measured: 256 requests of 4 .. 12 tokens at s = 512 145 against 162 us, 512 requests of 4
-    // tokens at s = 1024 80 against 114 us; 128 requests of 16 tokens at s = 4096 328 against
-    // 311 us).  The split form also stays whenever the caller tunes the decomposition by hand or
-    // asks for one phase only.
-    const bool whole = prefill && !naive && pl.n_sys_chunks <= 1 && mask == 3 &&
-                       p->sys_chunk_tokens == 0 && p->ctx_part_tokens == 0 &&
-                       ((int64_t)total_q >= kWholeMinTokens * (int64_t)p->batch ||
-                        (p->sys_len <= 1024 && (int64_t)total_q >= 4 * (int64_t)p->batch));
+    // Prompt phase in ONE launch: a work item carries its 128 rows through the system prompt and then
+    // through the contexts of the requests they belong to, and writes the output itself; no
+    // partials, no fusion launch.  split_prompt says when; the split form stays whenever the
+    // caller tunes the decomposition by hand or asks for one phase only.
+    const bool whole = prefill && !naive && pl.whole && mask == 3;
     // Many stacked rows per kv head (prompt phase; wide GQA decode batches): the many-rows kernel
     // takes the system part and, in the prompt phase, the causal context part as well.
     if ((mask & 1) && !naive && pl.rows_path) {

@@ -122,6 +122,15 @@ __device__ __forceinline__ void rows_item(const RowsArgs &a, const int block, un
         const int max_limit = ctx_len - q_len + last_row / a.G;
         key_end = min(min(ctx_len, max_limit + 1), key_begin + a.ctx_part);
         part_index = a.n_sys_chunks + part;
+        if (key_begin >= key_end) {
+            // Nothing of this part is visible to any row of the block (the number of parts comes from
+            // the host's bound on the lengths): the rows' partials end here, and no payload is written.
+            const int i = rb * kRowBlock + (int)threadIdx.x;
+            if ((int)threadIdx.x < kRowBlock && i < n_rows)
+                a.part_lse[(int64_t)part_index * a.rows + (int64_t)(token_base + i / a.G) * a.Hq +
+                           g * a.G + i % a.G] = __uint_as_float(kEndOfPartials);
+            return;                               // (uniform for the workgroup: before any barrier)
+        }
         first_blk = key_begin >> bsl;
         const int nblk = ((key_begin + a.ctx_part - 1) >> bsl) - first_blk + 1;
         const int32_t *bt = a.block_tables + (int64_t)req * a.max_blocks_per_seq;
@@ -245,6 +254,11 @@ __device__ __forceinline__ void rows_item(const RowsArgs &a, const int block, un
 #pragma unroll
         for (int off = 1; off < kWave; off <<= 1)
             wave_min_limit = min(wave_min_limit, __shfl_xor(wave_min_limit, off));
+        // A wavefront without a live row helps with the loads only (a request's last block holds 16
+        // rows when it brings 4 tokens of 4 heads: three of the four wavefronts).  (Whole items have
+        // such a wavefront in the last of their blocks only, and ran 1.5 % slower with this line.)
+        if constexpr (!WHOLE)
+            if (n - col >= n_rows) wave_limit = -1;
     };
     set_wave_limits();
 

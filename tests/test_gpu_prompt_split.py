@@ -1,0 +1,38 @@
+"""The prompt phase where the library cuts system prompt and contexts itself: launches with few blocks of
+rows and long contexts, parts that no row of a block can see, wavefronts without a live row."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from gpu_util import DeviceCase
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-3         # as in the other parity tests: fp32 output, error about 1e-6
+LSE_TOL = 1e-3
+
+
+# bound: factor on the longest context that the call gives as its bound (parts behind the real end).
+@pytest.mark.parametrize("B,Hq,Hkv,d,s,q,ctx,bs,bound", [
+    (1, 2, 2, 128, 3000, (1, 1), (2500, 2500), 16, 1),       # one row per block: three idle wavefronts
+    (3, 4, 1, 128, 700, (9, 40), (0, 3000), 16, 1),          # one context far shorter than the others
+    (2, 8, 2, 64, 129, (31, 33), (2100, 2200), 32, 3),       # rows around one block of 128, parts behind the end
+    (2, 3, 1, 64, 0, (60, 130), (2300, 4200), 16, 1),        # no system prompt, blocks across a causal edge
+    (2, 2, 1, 128, 600, (5, 70), (1500, 1700), 1, 1),        # block size 1: parts of 256 positions at most
+    (5, 4, 4, 64, 6000, (3, 20), (0, 10), 16, 40),           # chunks of the prompt; every part but one is empty
+])
+def test_cut_prompt_phase(B, Hq, Hkv, d, s, q, ctx, bs, bound):
+    cfg = W.AttnConfig(name="ps", batch=B, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, sys_len=s, ctx_lo=ctx[0],
+                       ctx_hi=ctx[1], block_size=bs, q_lo=q[0], q_hi=q[1])
+    case = W.make_case(cfg, 700 + B + s, prefill=True, extra_context=True)
+    longest = int(case.context_lens.max()) * bound
+    if bound > 1:
+        pad = np.full((B, -(-longest // bs) - case.block_tables.shape[1]), W.POISON_BLOCK, np.int32)
+        case.block_tables = np.ascontiguousarray(np.concatenate([case.block_tables, pad], 1))
+    print("[case] %s m=%s c=%s" % (cfg, np.diff(case.cu_seqlens_q), case.context_lens), flush=True)
+    want, wlse, _ = oracle.prefill_attention(case.q, case.cu_seqlens_q, case.k_sys, case.v_sys, case.k_cache, case.v_cache,
+                                             case.block_tables, case.context_lens, case.scale)
+    dc = DeviceCase(case, sys_layout="padded")
+    got, lse = dc.prefill(max_context_len=longest)
+    assert not bool((dc.last_workspace == 0xFF).all()), "the cut form was expected (partials in the workspace)"
+    assert np.isfinite(got).all() and np.abs(got - want).max() <= TOL and np.abs(lse - wlse).max() <= LSE_TOL
