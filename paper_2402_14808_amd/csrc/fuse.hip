@@ -127,35 +127,80 @@ __global__ __launch_bounds__(kThreads) void fuse_kernel(const FuseArgs a) {
     if (e == 0 && a.lse_out) a.lse_out[row] = W > 0.f ? (finite_or_zero(M) + log2f(W)) * kLn2 : -INFINITY;
 }
 
-// Cache append: one thread moves 16 bytes of one (token, kv head) row of K and of V.
-__global__ __launch_bounds__(kThreads) void cache_append_kernel(const AppendArgs a) {
-    const int cpr = a.head_dim / 8;                       // 16-byte chunks per row
-    const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const int64_t total = (int64_t)a.total_q * a.Hkv * cpr;
-    if (idx >= total) return;
-    const int chunk = (int)(idx % cpr);
-    const int g = (int)((idx / cpr) % a.Hkv);
-    const int token = (int)(idx / ((int64_t)cpr * a.Hkv));
-    int req = token, pos;
-    if (a.cu_seqlens_q) {
-        int lo = 0, hi = a.batch - 1;
-        while (lo < hi) {                                 // last request with cu_seqlens_q[r] <= token
-            const int mid = (lo + hi + 1) >> 1;
-            if (a.cu_seqlens_q[mid] <= token) lo = mid; else hi = mid - 1;
+// Cache append: a workgroup moves the rows of `tpw` consecutive tokens (K and V, all kv heads), a
+// thread up to eight 16-byte pieces at a time.  Bound: HBM for many tokens (every byte in once and out
+// once; one piece of K and V per thread, each with its own search for the request, ran 5222 tokens of 40
+// heads in 43 us, this form in 33), the chain of dependent reads for few: the pieces are read before
+// their place is known, and the request of a token is counted 64 requests at a time by the lanes of
+// one wavefront instead of searched by halving.
+constexpr int kAppendMaxTokens = 16;
+__global__ __launch_bounds__(kThreads) void cache_append_kernel(const AppendArgs a, const int tpw) {
+    __shared__ int64_t sm_dst[kAppendMaxTokens];         // element offset of (token, kv head 0), or -1
+    const int token0 = (int)blockIdx.x * tpw;
+    const int cpr_log2 = a.head_dim == 128 ? 4 : 3;       // 16-byte chunks per row
+    const int per_token = a.Hkv << cpr_log2;
+    const int n = min(tpw, a.total_q - token0) * per_token;
+    const int64_t head_stride = (int64_t)a.head_dim << a.block_size_log2;
+    constexpr int U = 4;
+    u32x4 k[U], v[U];
+    auto read = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * kThreads;
+            if (i >= n) continue;
+            const int t = i / per_token, in_token = i - t * per_token;
+            const int g = in_token >> cpr_log2, chunk = in_token & ((1 << cpr_log2) - 1);
+            const int64_t src = (int64_t)(token0 + t) * a.new_stride_token + (int64_t)g * a.new_stride_head + chunk * 8;
+            k[u] = *reinterpret_cast<const u32x4 *>(a.k_new + src);
+            v[u] = *reinterpret_cast<const u32x4 *>(a.v_new + src);
         }
-        req = lo;
-        const int q0 = a.cu_seqlens_q[req], q1 = a.cu_seqlens_q[req + 1];
-        pos = a.context_lens[req] - (q1 - q0) + (token - q0);
-    } else {
-        pos = a.context_lens[req] - 1;
+    };
+    read(threadIdx.x);
+    if (threadIdx.x < kWave) {
+        const int lane = (int)threadIdx.x;
+        const int token = token0 + lane;
+        int req = token;
+        if (a.cu_seqlens_q) {                             // requests that end at or before the token
+            req = 0;
+            for (int base = 0; base < a.batch; base += kWave) {
+                const int end = base + lane < a.batch ? a.cu_seqlens_q[base + lane + 1] : INT_MAX;
+                for (int t = 0; t < tpw; ++t) {
+                    const int ended = __builtin_popcountll(__builtin_amdgcn_ballot_w64(end <= token0 + t));
+                    if (lane == t) req += ended;
+                }
+            }
+            req = min(req, a.batch - 1);
+        }
+        if (lane < tpw && token < a.total_q) {
+            int pos = a.context_lens[req] - 1;
+            if (a.cu_seqlens_q) {
+                const int q0 = a.cu_seqlens_q[req], q1 = a.cu_seqlens_q[req + 1];
+                pos += 1 - (q1 - q0) + (token - q0);
+            }
+            int64_t dst = -1;                             // malformed lengths: write nothing
+            if (pos >= 0) {
+                const int64_t blk = a.block_tables[(int64_t)req * a.max_blocks_per_seq + (pos >> a.block_size_log2)];
+                const int bmask = (1 << a.block_size_log2) - 1;
+                dst = (((blk * a.Hkv) << a.block_size_log2) + (pos & bmask)) * (int64_t)a.head_dim;
+            }
+            sm_dst[lane] = dst;
+        }
     }
-    if (pos < 0) return;                                  // malformed lengths: write nothing
-    const int64_t blk = a.block_tables[(int64_t)req * a.max_blocks_per_seq + (pos >> a.block_size_log2)];
-    const int bmask = (1 << a.block_size_log2) - 1;
-    const int64_t dst = (((blk * a.Hkv + g) << a.block_size_log2) + (pos & bmask)) * (int64_t)a.head_dim + chunk * 8;
-    const int64_t src = (int64_t)token * a.new_stride_token + (int64_t)g * a.new_stride_head + chunk * 8;
-    *reinterpret_cast<u32x4 *>(a.k_cache + dst) = *reinterpret_cast<const u32x4 *>(a.k_new + src);
-    *reinterpret_cast<u32x4 *>(a.v_cache + dst) = *reinterpret_cast<const u32x4 *>(a.v_new + src);
+    __syncthreads();
+    for (int i0 = threadIdx.x; i0 < n; i0 += U * kThreads) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * kThreads;
+            if (i >= n) continue;
+            const int t = i / per_token, in_token = i - t * per_token;
+            const int g = in_token >> cpr_log2, chunk = in_token & ((1 << cpr_log2) - 1);
+            if (sm_dst[t] < 0) continue;
+            const int64_t to = sm_dst[t] + g * head_stride + chunk * 8;
+            *reinterpret_cast<u32x4 *>(a.k_cache + to) = k[u];
+            *reinterpret_cast<u32x4 *>(a.v_cache + to) = v[u];
+        }
+        read(i0 + U * kThreads);
+    }
 }
 
 // System-cache fill: same 16-byte moves, destination addressed by (position, kv head) strides.
@@ -183,10 +228,16 @@ hipError_t launch_system_fill(const SysFillArgs &a, hipStream_t stream) {
 }
 
 hipError_t launch_cache_append(const AppendArgs &a, hipStream_t stream) {
-    const int64_t total = (int64_t)a.total_q * a.Hkv * (a.head_dim / 8);
-    if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(cache_append_kernel, dim3((unsigned)((total + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, stream, a);
+    if (a.total_q == 0) return hipSuccess;
+    // about 1024 of the 16-byte chunks per workgroup (one round of U = 4), fewer where that would leave
+    // compute units idle
+    const int per_token = a.Hkv * (a.head_dim / 8);
+    int tpw = 1024 / per_token;
+    if (tpw > a.total_q / 512) tpw = a.total_q / 512;
+    if (tpw > kAppendMaxTokens) tpw = kAppendMaxTokens;
+    if (tpw < 1) tpw = 1;
+    hipLaunchKernelGGL(cache_append_kernel, dim3((unsigned)((a.total_q + tpw - 1) / tpw)), dim3(kThreads), 0,
+                       stream, a, tpw);
     return hipGetLastError();
 }
 
