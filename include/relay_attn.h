@@ -235,9 +235,10 @@ ra_status relay_attn_debug_timeline(const ra_params *p,
  *   the ones that share a compute unit with a system workgroup, which is known when the launch
  *   is exactly two workgroups per compute unit) every light workgroup takes
  *   L = (sys_tiles_total + N) / 256 - sys_workgroup_tiles tiles (0 if that is negative), split over
- *   its four wavefronts as above; if L / 4 < floor a light wavefront takes floor tiles when
- *   2 (L / 4) >= floor and none otherwise; none either if the light wavefronts together would
- *   exceed N.  The other ("heavy") wavefronts are a class that shares the rest, so that every
+ *   its four wavefronts as above; if L / 4 < floor its first q wavefronts take floor tiles each and the
+ *   others none, q = 0 .. 4 being the least number (with no more than N tiles in all) that makes the
+ *   larger of sys_workgroup_tiles + q floor and 2 ((N - tiles of the light ones) / heavy workgroups)
+ *   least.  No light wavefront takes any if together they would exceed N.  The other ("heavy") wavefronts are a class that shares the rest, so that every
  *   compute unit ends up with about the same number of tiles.  Should a span of either class then
  *   exceed (max_blocks_per_span - 1) * block_size / 32 tiles, the split into light and heavy is
  *   dropped.  Wavefronts whose span is empty do not count when segments of an item are numbered.

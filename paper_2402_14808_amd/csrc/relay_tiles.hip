@@ -516,7 +516,7 @@ __device__ __forceinline__ void run_context_wave(const TileArgs &a, unsigned cha
     // wavefront is left without work while others carry a rounded-up share.
     uint32_t lb = (uint32_t)a.ctx_light_begin, nl = (uint32_t)a.ctx_light_waves;
     const uint32_t n_heavy = (uint32_t)a.ctx_waves - nl;
-    uint32_t l_per_wg = 0, l_fix = 0, l_total = 0;
+    uint32_t l_per_wg = 0, l_fix = 0, l_total = 0, l_q = kWaves;
     if (nl > 0 && n_heavy > 0) {
         // tiles per compute unit, and what a system workgroup leaves of it for its neighbour
         const uint32_t per_unit = ((uint32_t)a.sys_tiles_total + n_tiles) / 256u;
@@ -524,9 +524,23 @@ __device__ __forceinline__ void run_context_wave(const TileArgs &a, unsigned cha
         if (l4 / kWaves >= floor_t) {
             l_per_wg = l4;
             l_total = l4 * (nl / kWaves);
-        } else {                                  // no spans shorter than the floor
-            l_fix = 2 * (l4 / kWaves) >= floor_t ? floor_t : 0;
-            l_total = l_fix * nl;
+        } else {
+            // No spans shorter than the floor: l_q of a light workgroup's four wavefronts take one.  The
+            // fullest unit is a light one with sys_wg_tiles + l_q * floor_t or a heavy one
+            // (two workgroups) with what is left; the number that makes the fuller of the two least.
+            // (None at all left 16 units with 120 tiles where the others had 86: 12 requests of
+            // 40 heads, contexts of 50 .. 145, a prompt of 16326.)
+            const uint32_t heavy_wgs = n_heavy / kWaves, step = floor_t * (nl / kWaves);
+            uint32_t least = 0xffffffffu;
+            l_fix = floor_t;
+            l_q = 0;
+            for (uint32_t q = 0; q <= (uint32_t)kWaves && q * step <= n_tiles; ++q) {
+                const uint32_t light = (uint32_t)a.sys_wg_tiles + q * floor_t;
+                const uint32_t heavy = 2 * ((n_tiles - q * step) / heavy_wgs);
+                const uint32_t fullest = light > heavy ? light : heavy;
+                if (fullest < least) least = fullest, l_q = q;
+            }
+            l_total = l_q * step;
         }
         if (l_total > n_tiles) l_per_wg = l_fix = l_total = 0;
     } else {
@@ -558,11 +572,16 @@ __device__ __forceinline__ void run_context_wave(const TileArgs &a, unsigned cha
     // Light wavefronts without a span drop out, and the others are numbered as if they were not
     // there (slot numbers count spans, and an item must not skip any).
     uint32_t uw = (uint32_t)w;
-    if (nl > 0 && l_total == 0) {
-        if (uw >= lb && uw < lb + nl) return;
-        if (uw >= lb + nl) uw -= nl;
-        lb = n_heavy;
-        nl = 0;
+    if (nl > 0 && l_total == 0) l_q = 0;
+    if (nl > 0 && l_q < (uint32_t)kWaves) {
+        const uint32_t left = (nl / kWaves) * l_q;
+        if (uw >= lb + nl) {
+            uw -= nl - left;
+        } else if (uw >= lb) {
+            if (((uw - lb) & 3u) >= l_q) return;
+            uw = lb + ((uw - lb) >> 2) * l_q + ((uw - lb) & 3u);
+        }
+        nl = left;
     }
     // tiles of wavefront i of a class, and the tiles of the class before it
     auto class_len = [](uint32_t i, uint32_t per_wg, uint32_t extra, uint32_t fix) -> uint32_t {
