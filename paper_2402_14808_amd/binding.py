@@ -146,13 +146,17 @@ def status_string(status: int) -> str:
     return load().relay_attn_status_string(int(status)).decode()
 
 
+# (What a call costs the host is what a small call costs: two launches of 8 and 2 us wait for 12 us of
+# interpreter otherwise.  The argument types turn plain addresses into pointers by themselves.)
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())     # no stream object made
 
 
 def make_params(q, out, k_sys, k_cache, block_tables, *, batch, softmax_scale,
