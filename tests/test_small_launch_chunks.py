@@ -1,0 +1,42 @@
+"""System chunks of small decode launches: multiples of four 32-position tiles where the rule asks for it."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2402_14808_amd as ra
+import workloads as W
+from gpu_util import DeviceCase
+from test_decode_plan import _params
+
+# batch, q heads, kv heads, head_dim, prompt, bound, tiles of a chunk
+CASES = [
+    (1, 16, 16, 64, 1625, 8140, 8),        # a turn less: 11 tiles without the rule
+    (2, 32, 32, 128, 3221, 188, 16),       # 13: one workgroup per unit instead of a few more
+    (12, 32, 8, 128, 6612, 46, 16),        # 13, stacked rows of a grouped model
+    (88, 16, 16, 64, 787, 35, 9),          # half of the units would hold a system workgroup: stays
+    (1, 4, 4, 64, 96, 64, 3),              # up to four tiles: stays
+]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,s,bound,tiles", CASES)
+def test_chunk_of_small_launches(B, Hq, Hkv, d, s, bound, tiles):
+    p = _params(B, Hq, Hkv, s, bound, d=d)
+    plan = ra.relay_attn_decode_plan(p)
+    if plan.compute_units != 256:
+        pytest.skip("the numbers are those of 256 compute units")
+    assert plan.sys_chunk_tokens == 32 * tiles and plan.num_sys_chunks == -(-s // (32 * tiles))
+    need = (plan.num_sys_chunks + plan.num_ctx_slots) * B * Hq * (d + 1) * 4
+    assert ra.relay_attn_workspace_bytes(p, B) >= need
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,Hq,Hkv,d,s,bound,tiles", CASES[:3])
+def test_decode_matches_oracle(B, Hq, Hkv, d, s, bound, tiles):
+    cfg = W.AttnConfig(name="sc", batch=B, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, sys_len=s, ctx_lo=1,
+                       ctx_hi=bound, block_size=16)
+    case = W.make_case(cfg, 60 + B)
+    print("[case] %s" % cfg, flush=True)
+    want, wlse, _ = oracle.decode_attention(case.q, case.k_sys, case.v_sys, case.k_cache, case.v_cache,
+                                            case.block_tables, case.context_lens, case.scale)
+    got, lse = DeviceCase(case).decode()
+    assert np.isfinite(got).all() and np.abs(got - want).max() <= 2e-3 and np.abs(lse - wlse).max() <= 1e-3
