@@ -156,7 +156,10 @@ def _stream():
     import torch
     if not torch.cuda.is_initialized():
         torch.cuda.init()
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())     # no stream object made
+    try:                                        # the same number without a stream object around it
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:                      # (names a torch release may change)
+        return torch.cuda.current_stream().cuda_stream
 
 
 def make_params(q, out, k_sys, k_cache, block_tables, *, batch, softmax_scale,
