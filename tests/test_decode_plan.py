@@ -22,55 +22,50 @@ def _params(B, Hq, Hkv, s, max_ctx, bs=16, d=128, **kw):
     return p
 
 
+def spans(plan, N, bs):
+    """Tiles of every context wavefront by the header's rule, and how the light ones came out: the q of the
+    rule (None where they share evenly or there are none) and whether the split into classes was dropped."""
+    W = plan.num_ctx_wavefronts
+    floor = plan.min_tiles_per_ctx_wavefront
+    cap = max(1, (plan.max_blocks_per_span - 1) * bs // 32)     # most tiles a span may have
+
+    def shared(R, n_wg):                        # wavefronts of a class of n_wg workgroups that shares R tiles
+        if R // n_wg // 4 < floor:
+            return [floor] * (4 * n_wg)
+        per_wg = [R // n_wg + (1 if v < R % n_wg else 0) for v in range(n_wg)]
+        return [Q // 4 + (1 if k < Q % 4 else 0) for Q in per_wg for k in range(4)]
+
+    lb, nl = plan.first_light_ctx_wavefront, plan.num_light_ctx_wavefronts
+    if nl == 0 or W == nl:
+        return shared(N, W // 4), None, False
+    l4 = max((plan.sys_tiles_total + N) // 256 - plan.sys_workgroup_tiles, 0)
+    heavy_wgs, q = (W - nl) // 4, None
+    if l4 // 4 >= floor:
+        light = [l4 // 4 + (1 if k < l4 % 4 else 0) for _ in range(nl // 4) for k in range(4)]
+    else:
+        step = floor * (nl // 4)
+        fullest = {k: max(plan.sys_workgroup_tiles + k * floor, 2 * ((N - k * step) // heavy_wgs))
+                   for k in range(5) if k * step <= N}
+        q = min(fullest, key=lambda k: (fullest[k], k))
+        light = [floor if k < q else 0 for _ in range(nl // 4) for k in range(4)]
+    if sum(light) > N:
+        light = [0] * nl
+    heavy = shared(N - sum(light), heavy_wgs)
+    if max(light + heavy) > cap:
+        return shared(N, W // 4), None, True
+    return heavy[:lb] + light + heavy[lb:], q, False
+
+
 def _replay(plan, lens, Hkv, bs):
     """Returns {(req, g): [(slot, tile_begin, tile_end), ...]} following the header's rule."""
     tiles = np.maximum(1, (lens + 31) // 32)
     N = int(tiles.sum()) * Hkv
     W = plan.num_ctx_wavefronts
-    floor = plan.min_tiles_per_ctx_wavefront
-    cap = max(1, (plan.max_blocks_per_span - 1) * bs // 32)     # most tiles a span may have
-
-    def class_len(i, per_wg, extra, fix):
-        if fix:
-            return fix
-        q = per_wg + (1 if (i >> 2) < extra else 0)
-        return (q >> 2) + (1 if (i & 3) < (q & 3) else 0)
-
-    lb, nl = W, 0
-    l_per_wg = l_fix = l_total = 0
-    if plan.num_light_ctx_wavefronts and W > plan.num_light_ctx_wavefronts:
-        lb, nl = plan.first_light_ctx_wavefront, plan.num_light_ctx_wavefronts
-        per_unit = (plan.sys_tiles_total + N) // 256
-        l4 = max(per_unit - plan.sys_workgroup_tiles, 0)
-        if l4 // 4 >= floor:
-            l_per_wg, l_total = l4, l4 * (nl // 4)
-        else:
-            l_fix = floor if 2 * (l4 // 4) >= floor else 0
-            l_total = l_fix * nl
-        if l_total > N:
-            l_per_wg = l_fix = l_total = 0
-
-    def share_heavy(n_waves):
-        rest, n_wg = N - l_total, n_waves // 4
-        per = rest // n_wg
-        if per // 4 >= floor:
-            return per, rest - per * n_wg, 0
-        return per, 0, floor
-    h_per_wg, h_extra, h_fix = share_heavy(W - nl if nl else W)
-    if nl:
-        most_l = l_fix if l_fix else (l_per_wg + 3) >> 2
-        most_h = h_fix if h_fix else (h_per_wg + (1 if h_extra else 0) + 3) >> 2
-        if most_l > cap or most_h > cap:
-            lb, nl = W, 0
-            l_per_wg = l_fix = l_total = 0
-            h_per_wg, h_extra, h_fix = share_heavy(W)
+    length, _, _ = spans(plan, N, bs)
     begins, at = [], 0
     for w in range(W):
         begins.append(at)
-        if lb <= w < lb + nl:
-            at += class_len(w - lb, l_per_wg, 0, l_fix)
-        else:
-            at += class_len(w if w < lb else w - nl, h_per_wg, h_extra, h_fix)
+        at += length[w]
     begins.append(at)
     assert at >= N
     first = {}
@@ -153,15 +148,59 @@ def test_context_stream_is_covered_exactly_once(B, Hq, Hkv, s, max_ctx, bs, dist
         else:
             lens = rng.integers(0, 40, size=B)
             lens[rng.integers(0, B)] = max_ctx
-        cover, tiles = _replay(plan, lens, Hkv, bs)
-        for (r, g), segs in cover.items():
-            segs.sort()
-            assert [sl for sl, _, _ in segs] == list(range(len(segs)))         # slots 0..n-1
-            assert len(segs) <= plan.num_ctx_slots
-            assert segs[0][1] == 0 and segs[-1][2] == tiles[r]
-            for (_, _, e0), (_, b1, _) in zip(segs, segs[1:]):
-                assert e0 == b1                                                 # contiguous
+        _check_cover(plan, lens, Hkv, bs)
 
+
+def _check_cover(plan, lens, Hkv, bs):
+    cover, tiles = _replay(plan, lens, Hkv, bs)
+    for (r, g), segs in cover.items():
+        segs.sort()
+        assert [sl for sl, _, _ in segs] == list(range(len(segs)))         # slots 0..n-1
+        assert len(segs) <= plan.num_ctx_slots
+        assert segs[0][1] == 0 and segs[-1][2] == tiles[r]
+        for (_, _, e0), (_, b1, _) in zip(segs, segs[1:]):
+            assert e0 == b1                                                 # contiguous
+
+
+def test_every_way_the_light_wavefronts_come_out_covers_the_tiles():
+    """Launches of exactly two workgroups per compute unit over lengths from empty to the bound: an even share
+    of the light wavefronts, q = 0 .. 4 of four with a span, and the split dropped for spans that would not
+    fit the block table, each met at least once."""
+    rng = np.random.Generator(np.random.PCG64(4))
+    seen = dict.fromkeys(("even", 0, 1, 2, 3, 4, "dropped"), 0)
+    for _ in range(4000):
+        G = int(rng.choice([1, 1, 2, 4, 7]))
+        Hkv = int(rng.choice([1, 2, 4, 8, 16, 32, 40, 52]))
+        B = int(np.exp(rng.uniform(0, np.log(160))))
+        s = int(np.exp(rng.uniform(np.log(200), np.log(20000))))
+        bs = int(rng.choice([1, 2, 4, 8, 16, 16, 32]))
+        mc = int(np.exp(rng.uniform(np.log(30), np.log(9000))))
+        try:
+            plan = ra.relay_attn_decode_plan(_params(B, G * Hkv, Hkv, s, mc, bs))
+        except ra.RelayAttnError as e:
+            assert e.status == ra.binding.RA_ERR_UNSUPPORTED
+            continue
+        if plan.compute_units != 256:
+            pytest.skip("light wavefronts exist on 256 compute units only")
+        if plan.num_light_ctx_wavefronts == 0:
+            continue
+        kind = rng.integers(0, 4)
+        if kind == 0:
+            lens = np.full(B, mc)
+        elif kind == 1:
+            lens = rng.integers(0, mc, size=B, endpoint=True)
+        elif kind == 2:
+            lens = rng.integers(0, max(1, mc // 8), size=B, endpoint=True)
+        else:
+            lens = rng.integers(0, 40, size=B)
+            lens[rng.integers(0, B)] = mc
+        lens = np.minimum(lens, mc)
+        _, q, dropped = spans(plan, int(np.maximum(1, (lens + 31) // 32).sum()) * Hkv, bs)
+        outcome = "dropped" if dropped else "even" if q is None else q
+        seen[outcome] += 1
+        if seen[outcome] <= 12:
+            _check_cover(plan, lens, Hkv, bs)
+    assert all(seen.values()), seen
 
 def plan_cap():
     return ra.relay_attn_decode_plan(_params(1, 1, 1, 0, 32)).max_blocks_per_span

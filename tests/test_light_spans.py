@@ -1,7 +1,5 @@
 """Context wavefronts next to a system workgroup that take a span in some of their four only: the spans the
 header's rule gives cover the tiles once, within the slots; on the GPU against the oracle."""
-import bisect
-
 import numpy as np
 import pytest
 
@@ -9,38 +7,7 @@ import oracle
 import paper_2402_14808_amd as ra
 import workloads as W
 from gpu_util import DeviceCase
-from test_decode_plan import _params
-
-
-def _spans(plan, n_tiles):
-    """(first tile, tiles) per wavefront that takes any, in order; and q."""
-    w, floor = plan.num_ctx_wavefronts, plan.min_tiles_per_ctx_wavefront
-    lb, nl = plan.first_light_ctx_wavefront, plan.num_light_ctx_wavefronts
-    heavy = (w - nl) // 4
-    light_l = max(0, (plan.sys_tiles_total + n_tiles) // 256 - plan.sys_workgroup_tiles)
-    assert nl and light_l // 4 < floor
-    step = floor * (nl // 4)
-    fullest = {q: max(plan.sys_workgroup_tiles + q * floor, 2 * ((n_tiles - q * step) // heavy))
-               for q in range(5) if q * step <= n_tiles}
-    q = min(fullest, key=lambda k: (fullest[k], k))
-    rest = n_tiles - q * step
-    per = rest // heavy
-    extra = rest - per * heavy if per // 4 >= floor else 0
-
-    def length(i):                              # of heavy wavefront i
-        if per // 4 < floor:
-            return floor
-        t = per + (1 if i // 4 < extra else 0)
-        return t // 4 + (1 if i % 4 < t % 4 else 0)
-    spans, at = [], 0
-    for i in range(w):
-        inside = lb <= i < lb + nl
-        n = (floor if (i - lb) % 4 < q else 0) if inside else length(i if i < lb else i - nl)
-        if n:
-            spans.append((at, n))
-            at += n
-    assert at >= n_tiles
-    return spans, q
+from test_decode_plan import _check_cover, _params, spans
 
 
 # batch, heads, prompt, bound, contexts, and the q they give
@@ -58,12 +25,9 @@ def test_spans_cover_every_item_within_its_slots(B, H, s, bound, ctx, want):
     if plan.compute_units != 256:
         pytest.skip("light wavefronts exist on 256 compute units only")
     lens = np.random.default_rng(B).integers(ctx[0], ctx[1] + 1, B)
-    tiles = np.repeat(np.maximum(1, (lens + 31) // 32), H)
-    spans, q = _spans(plan, int(tiles.sum()))
-    assert q == want
-    begins, ends = [b for b, _ in spans], np.cumsum(tiles)
-    for first, last in zip(ends - tiles, ends - 1):
-        assert bisect.bisect_right(begins, last) - bisect.bisect_right(begins, first) + 1 <= plan.num_ctx_slots
+    _, q, dropped = spans(plan, int(np.maximum(1, (lens + 31) // 32).sum()) * H, 16)
+    assert q == want and not dropped
+    _check_cover(plan, lens, H, 16)
 
 
 @pytest.mark.gpu
