@@ -14,7 +14,10 @@ namespace ra {
 // merge through LDS.  P = 1 where the rows alone fill the machine; with few rows that have many
 // partials each (a few requests with long contexts: 384 rows of up to 40) the batches of one row
 // would otherwise be one trip to memory after the other on a machine that is nearly empty.
-template <int D, bool MULTI, int P>
+// LATE: payloads behind the first `n_likely` partials are loaded once the log-sum-exps say that they are
+// there.  One trip more than loading both together, but no bytes of slots that were never written: a
+// bound far above the real lengths makes room for several times what a row uses.
+template <int D, bool MULTI, int P, bool LATE>
 __global__ __launch_bounds__(kThreads) void fuse_kernel(const FuseArgs a) {
     constexpr int TPR = D / 4;                  // threads per output row (4 elements each)
     constexpr int RPB = kThreads / (TPR * P);   // rows per block
@@ -44,15 +47,27 @@ __global__ __launch_bounds__(kThreads) void fuse_kernel(const FuseArgs a) {
         gap = a.n_sys_chunks - gap_at;
     }
     const int n = a.n_partials - gap;
+    [[maybe_unused]] const int likely = a.n_likely - gap;
     const int64_t oo = (int64_t)(row / a.Hq) * a.o_stride_token + (int64_t)(row % a.Hq) * a.o_stride_head + e;
     // One trip to memory per eight partials: log-sum-exps and payloads are loaded together and
     // merged with a running maximum (the same online rescaling the attention kernels use), rather
     // than reading all log-sum-exps first to find the maximum and then coming back for the rest.
-    // The slots behind an end mark hold anything; they are loaded with their batch and discarded.
+    // The slots behind an end mark hold anything; those of the batch are discarded (and, LATE, not loaded:
+    // there the log-sum-exps are fetched one round ahead, so that it stays one trip per round).
     // (v_exp_f32 as it is: a weight below the normal range cannot reach a sum that holds a 1.)
     float M = -INFINITY, W = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     int end = INT_MAX;
+    auto slot_of = [&](int p, bool read) -> int64_t {          // of the row's partial p; slot 0 if it is not read
+        const int at = MULTI && p >= gap_at ? p + gap : p;
+        return (int64_t)(read ? at : 0) * a.rows + row;
+    };
+    auto payload = [&](int64_t slot) { return *reinterpret_cast<const f32x4 *>(a.part_o + slot * D + e); };
+    [[maybe_unused]] float l_next[U];
+    if constexpr (LATE) {
+#pragma unroll
+        for (int j = 0; j < U; ++j) l_next[j] = a.part_lse[slot_of(part * U + j, part * U + j < n)];
+    }
     for (int round = 0; round * (P * U) < n; ++round) {
         const int p0 = round * (P * U) + part * U;
         float l[U];
@@ -60,10 +75,14 @@ __global__ __launch_bounds__(kThreads) void fuse_kernel(const FuseArgs a) {
 #pragma unroll
         for (int j = 0; j < U; ++j) {
             const bool ok = p0 + j < n;
-            const int p = MULTI && p0 + j >= gap_at ? p0 + j + gap : p0 + j;
-            const int64_t slot = (int64_t)(ok ? p : 0) * a.rows + row;
-            l[j] = a.part_lse[slot];
-            o[j] = *reinterpret_cast<const f32x4 *>(a.part_o + slot * D + e);
+            if constexpr (LATE) {
+                l[j] = l_next[j];
+                if (round == 0) o[j] = payload(slot_of(p0 + j, p0 + j < likely));
+            } else {
+                const int64_t slot = slot_of(p0 + j, ok);
+                l[j] = a.part_lse[slot];
+                o[j] = payload(slot);
+            }
             l[j] = ok ? l[j] : -INFINITY;
         }
 #pragma unroll
@@ -74,6 +93,14 @@ __global__ __launch_bounds__(kThreads) void fuse_kernel(const FuseArgs a) {
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < P; ++k) end = min(end, sm_end[round & 1][k]);
+        }
+        if constexpr (LATE) {
+            const int last = min(end, n), p1 = p0 + P * U;
+#pragma unroll
+            for (int j = 0; j < U; ++j)
+                if ((round > 0 || p0 + j >= likely) && p0 + j < last) o[j] = payload(slot_of(p0 + j, true));
+#pragma unroll
+            for (int j = 0; j < U; ++j) l_next[j] = p1 < last ? a.part_lse[slot_of(p1 + j, p1 + j < n)] : 0.f;
         }
         float Mb = M;
 #pragma unroll
@@ -241,6 +268,13 @@ hipError_t launch_cache_append(const AppendArgs &a, hipStream_t stream) {
     return hipGetLastError();
 }
 
+template <int D, bool MULTI, int P>
+static void launch_fuse_form(const FuseArgs &a, bool late, const dim3 &grid, hipStream_t stream) {
+    if (late) hipLaunchKernelGGL((fuse_kernel<D, MULTI, P, true>), grid, dim3(kThreads), 0, stream, a);
+    else hipLaunchKernelGGL((fuse_kernel<D, MULTI, P, false>), grid, dim3(kThreads), 0, stream, a);
+}
+
+constexpr int64_t kLateBytes = 12 << 20;
 template <int D>
 static void launch_fuse_d(const FuseArgs &a, hipStream_t stream) {
     constexpr int TPR = D / 4, P = kThreads / TPR;      // split form: one row per workgroup
@@ -248,12 +282,21 @@ static void launch_fuse_d(const FuseArgs &a, hipStream_t stream) {
     // this kind at once: split (384 rows of up to 40 partials in
     // 131 slots take 5.2 us; three batches one after the other, 24 slots, took 5.1).
     const bool split = a.n_partials > 16 && a.rows <= 2048;
+    // Late payloads where the first round would load more than 12 MiB beyond the likely partials, which
+    // is about what the extra trip to memory costs.  Measured, whole call, early / late payloads: 1024
+    // rows of 32 requests, bound 16128, one of them that long and the others 100 positions 37.4 / 32.5
+    // us; 64 requests of 32/8 heads with contexts of 100 .. 1000 under a bound of 16400 48.6 / 46.1
+    // us; but 256 rows that fill 130 slots (8 requests of 32/4 heads, one of 30000 positions) 30.1 / 33.0,
+    // and one request of 90 positions 10.2 / 10.6.
+    const int first = split ? 8 * P : 8;
+    const int64_t beyond = (a.n_partials < first ? a.n_partials : first) - a.n_likely;
+    const bool late = beyond * a.rows * D * 4 > kLateBytes;
     const bool multi = a.n_prefixes > 1;
-    const dim3 grid(split ? a.rows : (a.rows + P - 1) / P), block(kThreads);
-    if (split && multi) hipLaunchKernelGGL((fuse_kernel<D, true, P>), grid, block, 0, stream, a);
-    else if (split) hipLaunchKernelGGL((fuse_kernel<D, false, P>), grid, block, 0, stream, a);
-    else if (multi) hipLaunchKernelGGL((fuse_kernel<D, true, 1>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((fuse_kernel<D, false, 1>), grid, block, 0, stream, a);
+    const dim3 grid(split ? a.rows : (a.rows + P - 1) / P);
+    if (split && multi) launch_fuse_form<D, true, P>(a, late, grid, stream);
+    else if (split) launch_fuse_form<D, false, P>(a, late, grid, stream);
+    else if (multi) launch_fuse_form<D, true, 1>(a, late, grid, stream);
+    else launch_fuse_form<D, false, 1>(a, late, grid, stream);
 }
 
 hipError_t launch_fuse(const FuseArgs &a, int head_dim, hipStream_t stream) {

@@ -11,7 +11,7 @@ namespace ra {
 // attention output (fp32) and part_lse[p * rows + r] its log-sum-exp in the base-2
 // domain (log2 of the sum of 2^(logit * scale * log2 e)); -inf marks an empty partial.
 // A row takes its context slots from the first one on; where it leaves some unused, the log-sum-exp
-// of the first unused one is kEndOfPartials and the ones behind it are never written.  (A number
+// of the first unused one is kEndOfPartials and the ones behind it hold anything.  (A number
 // that is not one and that no computation on bf16 data produces: the hardware's own has a zero low
 // half, and so has one that came in with the data.)
 constexpr uint32_t kEndOfPartials = 0x7fedcba9u;
@@ -123,6 +123,9 @@ struct FuseArgs {                // relay fusion (Alg. 1; Eq. 11 generalised to 
     float *lse_out;
     int64_t o_stride_token, o_stride_head;
     int rows, Hq, n_partials, out_is_fp32;
+    // partials below this one are expected to be there (all prefixes at their longest; 1 .. n_partials):
+    // the fusion may load them before it knows where a row ends
+    int n_likely;
     // several shared prefixes: rows of tokens below pfx_token_end[p] (and not below the previous
     // end) have only pfx_chunks[p] of the n_sys_chunks system partials
     int n_prefixes, n_sys_chunks, pfx_token_end[kMaxPrefixes], pfx_chunks[kMaxPrefixes];

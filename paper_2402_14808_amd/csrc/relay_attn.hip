@@ -30,6 +30,7 @@ struct Plan {
     int n_sys_chunks;
     int ctx_part;         // context positions per work item (prompt phase, per-request kernel)
     int n_ctx_parts;      // context partial slots per row
+    int n_ctx_likely;     // of these, the ones that lengths near the bound take (0: all); see FuseArgs
     int ctx_wgs;          // decode: context workgroups (four wavefronts each) in the tile launch
     int ctx_t_floor;      // decode: least tiles per context wavefront, bounds the slots per row
     bool paired;          // decode: the launch is exactly two workgroups per compute unit
@@ -379,8 +380,9 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
                 // floor near t_est would leave most context wavefronts without work (a batch
                 // with lengths uniform in [64, 1024] has half the tiles the plan assumed; one of
                 // 1500 .. 15000 under a bound of 16400 has half of them as well).  So the floor is
-                // an eighth of t_est.  Slots that the real lengths do not need cost workspace only
-                // (the fusion reads the ones that were written); the partials stay within the
+                // an eighth of t_est.  Slots that the real lengths do not need cost workspace, and in
+                // the fusion the log-sum-exps of a round (their payloads are left alone where they
+                // would be many, see launch_fuse_d); the partials stay within the
                 // static scratch unless even a floor of t_est itself takes more.
                 // (12 requests, 8 kv heads, contexts 1500 .. 15000: 95.9 -> 73.5 us with
                 // spans of 12 tiles on every wavefront instead of 24 on half of them)
@@ -391,6 +393,7 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
                 int64_t wide = (t_max + t_low - 1) / t_low + 1;
                 const int64_t room = (int64_t)((kStaticScratchBytes - 512) / ((size_t)pl.rows * (d * 4 + 4))) -
                                      pl.n_sys_chunks;
+                pl.n_ctx_likely = (int)slots;
                 if (wide > room) wide = room;
                 if (wide > slots) slots = wide;
                 pl.n_ctx_parts = (int)slots;
@@ -426,6 +429,7 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
         else if (prefill) pl.ctx_part = hand_set ? longest_part(p) : split.part;
         else pl.ctx_part = 256;
         pl.n_ctx_parts = ceil_div(pl.max_ctx, pl.ctx_part);
+        if (prefill) pl.n_ctx_likely = 1;       // (every context has a first part; many rows hide the trip)
         // a context part may touch at most kMaxPartBlocks blocks (the per-item block-id table in
         // LDS); parts start at multiples of ctx_part, which are block boundaries only when the
         // block size divides it
@@ -722,6 +726,7 @@ ra_status run(const ra_params *p, const void *q, const int32_t *cu_seqlens_q, in
         f.rows = pl.rows;
         f.Hq = p->num_q_heads;
         f.n_partials = pl.n_sys_chunks + pl.n_ctx_parts;
+        f.n_likely = pl.n_sys_chunks + (pl.n_ctx_likely > 0 ? pl.n_ctx_likely : pl.n_ctx_parts);
         f.n_sys_chunks = pl.n_sys_chunks;
         f.n_prefixes = num_prefixes;
         f.req_prefix = num_prefixes > 1 ? req_prefix : nullptr;
