@@ -105,11 +105,14 @@ __device__ __forceinline__ void rows_item(const RowsArgs &a, const int block, un
         key_end = min(sys_len, key_begin + a.sys_chunk);
         part_index = chunk;
     } else {
+        // The kv head varies fastest and the part slowest: workgroups are dealt to the eight XCDs in turn, and
+        // with the part (or the row block) in front, eight parts per context put every context's first
+        // part on one XCD and the others' parts behind the real lengths, which end at once, on the rest.
         int j = block - a.n_sys_items;
-        const int part = j % a.n_ctx_parts;  j /= a.n_ctx_parts;
+        g = j % a.Hkv;                       j /= a.Hkv;
         rb = j % a.n_ctx_rowblocks;          j /= a.n_ctx_rowblocks;
-        g = j % a.Hkv;
-        req = j / a.Hkv;
+        req = j % a.batch;
+        const int part = j / a.batch;
         const int q0 = a.cu_seqlens_q[req];
         q_len = a.cu_seqlens_q[req + 1] - q0;
         token_base = q0;
@@ -120,13 +123,15 @@ __device__ __forceinline__ void rows_item(const RowsArgs &a, const int block, un
         // the last row of this block sees the most: positions <= ctx_len - q_len + its token index
         const int last_row = min(n_rows, (rb + 1) * kRowBlock) - 1;
         const int max_limit = ctx_len - q_len + last_row / a.G;
-        key_end = min(min(ctx_len, max_limit + 1), key_begin + a.ctx_part);
+        const int seen = max(0, min(ctx_len, max_limit + 1));
+        key_end = min(seen, key_begin + a.ctx_part);
         part_index = a.n_sys_chunks + part;
-        if (key_begin >= key_end) {
+        if (key_begin >= seen) {
             // Nothing of this part is visible to any row of the block (the number of parts comes from
-            // the host's bound on the lengths): the rows' partials end here, and no payload is written.
+            // the host's bound on the lengths): the first such part ends the rows' partials, and no
+            // payload is written.
             const int i = rb * kRowBlock + (int)threadIdx.x;
-            if ((int)threadIdx.x < kRowBlock && i < n_rows)
+            if (key_begin - a.ctx_part < seen && (int)threadIdx.x < kRowBlock && i < n_rows)
                 a.part_lse[(int64_t)part_index * a.rows + (int64_t)(token_base + i / a.G) * a.Hq +
                            g * a.G + i % a.G] = __uint_as_float(kEndOfPartials);
             return;                               // (uniform for the workgroup: before any barrier)
