@@ -148,7 +148,18 @@ PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx) {
     const double row_bytes = (double)total_q * p->num_q_heads * p->head_dim * 4;
     const double step_us = p->head_dim == 128 ? 1.5 : 1.1;     // 64 keys by 128 rows, a compute unit to itself
     const double cus = device_compute_units();
-    const double mean_new = (double)total_q / batch, ctx = 0.85 * max_ctx;      // (lengths live on the device)
+    // The lengths live on the device.  Known of them is the bound, which may be a table's capacity, and
+    // that the contexts of all requests together fit the cache (a num_blocks that does not even hold the
+    // new tokens was not filled in; contexts that share blocks may be longer, which costs time only).
+    // Going by the bound alone, a loose one took launches apart that are best left whole and left few
+    // chunks to prompts that the launch then waited for: 32 requests of 32 heads with 40 .. 200 new
+    // tokens, s = 600, in tables of 8192 positions 215 us against 126, 4 requests of 32/8 heads with
+    // 10 .. 60 behind 100 .. 200, s = 1024, 40 against 25.
+    const double mean_new = (double)total_q / batch;
+    double held = (double)p->num_blocks * p->block_size;
+    if (held < total_q) held = (double)batch * max_ctx;
+    const double ctx_most = held < max_ctx ? held : max_ctx;
+    const double ctx = held / batch < 0.85 * max_ctx ? held / batch : 0.85 * max_ctx;
     // items per context part: blocks of 128 stacked rows of an average request, times kv heads and requests
     const int64_t ctx_base = batch * hkv * (((total_q + batch - 1) / batch * G + 127) / 128);
     const double steps = ((double)base * s + ctx_base * ctx) / 64;
@@ -164,6 +175,9 @@ PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx) {
     const int64_t least_parts = max_ctx > 0 ? (max_ctx + longest - 1) / longest : 1;
     // (no more items than a launch index holds, whatever the longest request brings)
     const int64_t rb_most = batch * hkv * ((total_q * G + 127) / 128);
+    // (and no more workspace than twice the coarsest cut's, or 64 MiB)
+    int64_t most_partials = (int64_t)((64 << 20) / row_bytes);
+    if (most_partials < 2 * (least_parts + 1)) most_partials = 2 * (least_parts + 1);
     for (int64_t nc = 1; nc <= most_chunks; nc += (nc + 1) / 2) {
         const int64_t chunk = (((s > 0 ? s : 1) + nc - 1) / nc + 127) / 128 * 128;
         const int64_t n_chunks = (s + chunk - 1) / chunk;
@@ -171,8 +185,9 @@ PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx) {
             int64_t part = (((max_ctx > 0 ? max_ctx : 1) + np - 1) / np + 127) / 128 * 128;
             if (part > longest) part = longest;
             if (np > least_parts && (rb_most * (np + 1) > (1 << 30) || base * n_chunks > (1 << 30))) break;
+            if (np > least_parts && n_chunks + (max_ctx + part - 1) / part > most_partials) break;
             const double parts = max_ctx > 0 ? ceil(ctx / part) : 0;
-            const double t_sys = (double)(chunk < s ? chunk : s) / 64, t_ctx = (double)(part < max_ctx ? part : max_ctx) / 64;
+            const double t_sys = (double)(chunk < s ? chunk : s) / 64, t_ctx = (part < ctx_most ? part : ctx_most) / 64;
             const double us = launch_us(t_sys > t_ctx ? t_sys : t_ctx, steps, base * n_chunks + ctx_base * parts) +
                               row_bytes * (n_chunks + parts) * (2 / 5e6) + 12;
             if (us < best_us) best_us = us, best.chunk = (int)chunk, best.part = (int)part;
@@ -187,8 +202,8 @@ PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx) {
     // requests of 300 .. 1000 tokens behind contexts of 3000 .. 8000: 323 us whole, 216 .. 225 cut).
     const bool few_blocks = (400 + base / 2) / base > 1 && s > 512;
     const double met = mean_new > 0 ? 128.0 / G / mean_new + 1 : 1;     // requests with rows in a block
-    const double walk = (double)s + (met < batch ? met : batch) * max_ctx;
-    const double walk_mean = (double)s + (met < batch ? met : batch) * ctx;
+    const double reqs = met < batch ? met : batch;
+    const double walk = s + (reqs * ctx_most < held ? reqs * ctx_most : held), walk_mean = s + reqs * ctx;
     best.whole = !few_blocks && (total_q >= kWholeMinTokens * batch || (s <= 1024 && total_q >= 4 * batch)) &&
                  (walk <= 2048 || launch_us(walk / 64, walk_mean / 64 * base, (double)base) <= best_us);
     if (best.whole) best.chunk = (int)((s + 127) / 128 * 128), best.part = longest;

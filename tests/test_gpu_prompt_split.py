@@ -36,3 +36,26 @@ def test_cut_prompt_phase(B, Hq, Hkv, d, s, q, ctx, bs, bound):
     got, lse = dc.prefill(max_context_len=longest)
     assert not bool((dc.last_workspace == 0xFF).all()), "the cut form was expected (partials in the workspace)"
     assert np.isfinite(got).all() and np.abs(got - want).max() <= TOL and np.abs(lse - wlse).max() <= LSE_TOL
+
+
+@pytest.mark.parametrize("bound", [0, 8192, 65536])        # 0: exactly the longest context
+def test_new_conversations_under_a_loose_bound_stay_one_launch(bound):
+    """Contexts that are the new tokens only, a bound that is the capacity of the block table: how the launch
+    is cut goes by the lengths the cache can hold, not by the bound alone."""
+    cfg = W.AttnConfig(name="nc", batch=2, num_q_heads=32, num_kv_heads=8, head_dim=128, sys_len=300, ctx_lo=0, ctx_hi=0,
+                       block_size=16, q_lo=300, q_hi=900)
+    case = W.make_case(cfg, 750, prefill=True)
+    if bound:
+        pad = np.full((2, bound // 16 - case.block_tables.shape[1]), W.POISON_BLOCK, np.int32)
+        case.block_tables = np.ascontiguousarray(np.concatenate([case.block_tables, pad], 1))
+    total = int(case.cu_seqlens_q[-1])
+    print("[case] %s tokens %d bound %d" % (cfg, total, bound), flush=True)
+    rows = np.array([(t, h) for t in (0, 1, total // 2, total - 1) for h in (0, 31)])
+    want, wlse, _ = oracle.prefill_attention(case.q, case.cu_seqlens_q, case.k_sys, case.v_sys, case.k_cache, case.v_cache,
+                                             case.block_tables, case.context_lens, case.scale, rows=rows)
+    dc = DeviceCase(case)
+    got, lse = dc.prefill(max_context_len=bound or None)
+    untouched = bool((dc.last_workspace == 0xFF).all())     # (a comparison inside the assertion would be unpacked)
+    assert untouched, "the one-launch form was expected (workspace untouched)"
+    r = (rows[:, 0], rows[:, 1])
+    assert np.isfinite(got).all() and np.abs(got[r] - want).max() <= TOL and np.abs(lse[r] - wlse).max() <= LSE_TOL
