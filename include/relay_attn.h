@@ -110,6 +110,10 @@ typedef struct {
  * launch and the fusion launch; it needs no initialisation and may be reused
  * by any later call that does not overlap in time.  Returns 0 if the
  * parameters are invalid.  Host only, no launch.
+ *   The size belongs to these parameters and does not only rise with the
+ * batch.  A call whose workspace is smaller takes fewer partials where that
+ * fits (somewhat slower; the results agree within the tolerance, not bit for
+ * bit) and returns RA_ERR_WORKSPACE_TOO_SMALL otherwise.
  */
 size_t relay_attn_workspace_bytes(const ra_params *p, int32_t total_q);
 
@@ -121,7 +125,7 @@ size_t relay_attn_workspace_bytes(const ra_params *p, int32_t total_q);
  *   lse_out  nullable; [batch][Hq] fp32, natural-log log-sum-exp of the scaled
  *            logits over all sys_len + context_lens[i] positions (Eq. 12)
  * A request with sys_len + context_lens[i] == 0 gets a zero output row and
- * lse = -inf.  workspace must be 256-byte aligned and at least
+ * lse = -inf.  workspace must be 256-byte aligned; it should hold
  * relay_attn_workspace_bytes(p, batch) bytes.
  */
 ra_status relay_attn_decode(const ra_params *p,

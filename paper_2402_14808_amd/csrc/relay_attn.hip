@@ -127,11 +127,28 @@ int longest_part(const ra_params *p) {
     return part < 128 ? 128 : part;
 }
 
+// New tokens per request, on average, from which a block of 128 rows does not meet too many requests to
+// go through their contexts one after the other.
+bool many_new_tokens(const ra_params *p, int32_t total_q) {
+    return total_q >= (int64_t)kWholeMinTokens * p->batch || (p->sys_len <= 1024 && total_q >= (int64_t)4 * p->batch);
+}
+
 // How the prompt phase is cut, where the caller leaves it to the library.
 struct PromptSplit {
     bool whole;          // one launch of items that go through prompt and contexts (see `run`)
     int chunk, part;     // otherwise: system positions and context positions of an item
 };
+
+// The fewest partials: about 400 workgroups of at least 512 system positions, the longest context parts;
+// one launch where that is one chunk (see split_prompt for its limits).
+PromptSplit coarse_split(const ra_params *p, int32_t total_q) {
+    const int base = p->num_kv_heads * ceil_div(total_q * (p->num_q_heads / p->num_kv_heads), 128);
+    const int most = ceil_div(p->sys_len, 512);
+    int n = (400 + base / 2) / base;
+    if (n > most) n = most;
+    if (n < 1) n = 1;
+    return {n == 1 && many_new_tokens(p, total_q), ceil_div(ceil_div(p->sys_len, n), 128) * 128, longest_part(p)};
+}
 
 // A prompt-phase launch takes about as long as the larger of its longest item and its work per
 // compute unit, plus the thin end of the launch; a finer cut shortens the first and the last
@@ -204,7 +221,7 @@ PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx) {
     const double met = mean_new > 0 ? 128.0 / G / mean_new + 1 : 1;     // requests with rows in a block
     const double reqs = met < batch ? met : batch;
     const double walk = s + (reqs * ctx_most < held ? reqs * ctx_most : held), walk_mean = s + reqs * ctx;
-    best.whole = !few_blocks && (total_q >= kWholeMinTokens * batch || (s <= 1024 && total_q >= 4 * batch)) &&
+    best.whole = !few_blocks && many_new_tokens(p, total_q) &&
                  (walk <= 2048 || launch_us(walk / 64, walk_mean / 64 * base, (double)base) <= best_us);
     if (best.whole) best.chunk = (int)((s + 127) / 128 * 128), best.part = longest;
     if (best.chunk < 128) best.chunk = 128;
@@ -218,10 +235,13 @@ constexpr int kMinWaveTiles = 4;
 constexpr int kRowsSysMinTiles = 8;
 
 // Work decomposition; a pure function of (params, total_q) so that the workspace size the
-// caller asked for and the one the launch uses always agree.
+// caller asked for and the one the launch uses always agree.  A `budget` below that size asks for
+// the fewest partials: the cut that a caller's workspace of fixed size, made for another batch, may
+// still hold (the size does not only rise with the batch).
 Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q_len,
-               int64_t sys_base_items = 0, bool allow_rows_sys = true) {
+               int64_t sys_base_items = 0, bool allow_rows_sys = true, size_t budget = SIZE_MAX) {
     Plan pl{};
+    const bool tight = budget != SIZE_MAX;
     const bool prefill = kind == kPrefill;
     // Wavefronts the chip holds at once with the tile kernel's two workgroups of four per
     // compute unit.
@@ -337,7 +357,7 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
                 // workgroup per unit down to it (two requests of 32 heads at 3221, 280 -> 248 workgroups,
                 // 20.4 -> 17.7 us; without that effect 13.4 -> 14.0, 10 requests of 28/4 heads at 1989).
                 const int64_t tiles = chunk / 32, down = tiles / 4 * 4, up = down + 4;
-                if (t_star16 <= 40 && tiles > 4 && down < tiles) {
+                if (!tight && t_star16 <= 40 && tiles > 4 && down < tiles) {
                     const int64_t like16 = up * 4 > t_star16 ? up * 4 : t_star16;
                     const int64_t units = kWorkgroupSlots / 2, ctx_like = (ctx_tiles * 16 + 4 * like16 - 1) / (4 * like16);
                     auto wgs_at = [&](int64_t t) { return base_items * ((sys_tiles + t - 1) / t); };
@@ -406,7 +426,8 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
                 int64_t t_low = (t_est + 7) / 8;
                 if (t_low < kMinWaveTiles) t_low = kMinWaveTiles < t_est ? kMinWaveTiles : t_est;
                 int64_t wide = (t_max + t_low - 1) / t_low + 1;
-                const int64_t room = (int64_t)((kStaticScratchBytes - 512) / ((size_t)pl.rows * (d * 4 + 4))) -
+                const size_t most = budget < kStaticScratchBytes ? budget : kStaticScratchBytes;
+                const int64_t room = (int64_t)((most > 512 ? most - 512 : 0) / ((size_t)pl.rows * (d * 4 + 4))) -
                                      pl.n_sys_chunks;
                 pl.n_ctx_likely = (int)slots;
                 if (wide > room) wide = room;
@@ -420,29 +441,18 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
         return pl;
     }
 
-    PromptSplit split{};
     const bool hand_set = p->sys_chunk_tokens != 0 || p->ctx_part_tokens != 0;
-    if (prefill && !hand_set) split = split_prompt(p, total_q, pl.max_ctx);
-    pl.whole = split.whole;
+    PromptSplit split{false, 0, 256};
+    if (prefill && !hand_set && !tight) split = split_prompt(p, total_q, pl.max_ctx);
+    else if (p->sys_len > 0 || prefill) split = coarse_split(p, total_q);
+    if (!prefill) split.part = 256;
+    pl.whole = prefill && !hand_set && split.whole;
     if (p->sys_len > 0) {
-        int chunk = p->sys_chunk_tokens;
-        if (chunk == 0 && (hand_set || !prefill)) {
-            // (the other length is set by hand) about 400 workgroups of at least 512 positions
-            const int64_t base_items = (int64_t)p->num_kv_heads * pl.n_sys_rowblocks;
-            int64_t n_chunks = (400 + base_items / 2) / base_items;
-            const int64_t max_chunks = ceil_div(p->sys_len, 512);
-            if (n_chunks > max_chunks) n_chunks = max_chunks;
-            if (n_chunks < 1) n_chunks = 1;
-            chunk = ceil_div(ceil_div(p->sys_len, (int)n_chunks), 128) * 128;
-        }
-        if (chunk == 0) chunk = split.chunk;
-        pl.sys_chunk = chunk;
-        pl.n_sys_chunks = ceil_div(p->sys_len, chunk);
+        pl.sys_chunk = p->sys_chunk_tokens > 0 ? p->sys_chunk_tokens : split.chunk;
+        pl.n_sys_chunks = ceil_div(p->sys_len, pl.sys_chunk);
     }
     if (pl.max_ctx > 0) {
-        if (p->ctx_part_tokens > 0) pl.ctx_part = p->ctx_part_tokens;
-        else if (prefill) pl.ctx_part = hand_set ? longest_part(p) : split.part;
-        else pl.ctx_part = 256;
+        pl.ctx_part = p->ctx_part_tokens > 0 ? p->ctx_part_tokens : split.part;
         pl.n_ctx_parts = ceil_div(pl.max_ctx, pl.ctx_part);
         if (prefill) pl.n_ctx_likely = 1;       // (every context has a first part; many rows hide the trip)
         // a context part may touch at most kMaxPartBlocks blocks (the per-item block-id table in
@@ -512,11 +522,17 @@ ra_status run(const ra_params *p, const void *q, const int32_t *cu_seqlens_q, in
         if (mt > 1) read_once = false;          // several row tiles re-read the same K/V
     }
     const PlanKind kind = cu_seqlens_q ? kPrefill : naive ? kNaiveDecode : kRelayDecode;
-    Plan pl = make_plan(p, total_q, kind, max_q_len, num_prefixes > 1 ? sys_base_items : 0);
     // A caller sizes the workspace without knowing the grouping; should the grouping-aware plan
     // need more than that, the grouping-blind one (which is what the size was computed from) is used.
-    if (num_prefixes > 1 && !pl.unsupported && pl.bytes > workspace_bytes)
-        pl = make_plan(p, total_q, kind, max_q_len, 0, false);
+    // Where the workspace is smaller than either, the cut with the fewest partials may still fit it.
+    const bool multi = num_prefixes > 1;
+    Plan pl{};
+    for (size_t budget : {SIZE_MAX, workspace_bytes}) {
+        pl = make_plan(p, total_q, kind, max_q_len, multi ? sys_base_items : 0, true, budget);
+        if (multi && !pl.unsupported && pl.bytes > workspace_bytes)
+            pl = make_plan(p, total_q, kind, max_q_len, 0, false, budget);
+        if (pl.unsupported || pl.bytes <= workspace_bytes) break;
+    }
     if (pl.unsupported) return RA_ERR_UNSUPPORTED;
     if (total_q > 0) {
         if (!q || !out || !context_lens) return RA_ERR_INVALID_ARG;
