@@ -45,3 +45,36 @@ def test_decode_matches_oracle(B, H, s, bound, ctx, want):
     got, lse = DeviceCase(case).decode(max_context_len=bound)
     r = (rows[:, 0], rows[:, 1])
     assert np.isfinite(got).all() and np.abs(got[r] - want_o).max() <= 2e-3 and np.abs(lse[r] - want_l).max() <= 1e-3
+
+
+# contexts whose items run from heavy wavefronts into light ones, out of them, or through all of them
+@pytest.mark.gpu
+@pytest.mark.parametrize("Hq,Hkv,s,bound,lens,want", [
+    (32, 8, 855, 18011, [12720], 1),
+    (32, 4, 15810, 8167, [28, 18, 7112, 13, 7], 1),
+    (32, 8, 18073, 10567, [9016, 32], 2),
+    (64, 8, 19480, 22586, [13103], 3),
+    (64, 8, 15593, 18944, [16444], 4),
+    (32, 8, 756, 30778, [28363], None),          # an even share
+])
+def test_a_context_across_both_classes_matches_oracle(Hq, Hkv, s, bound, lens, want):
+    B, d = len(lens), 64
+    plan = ra.relay_attn_decode_plan(_params(B, Hq, Hkv, s, bound, d=d))
+    tiles = np.maximum(1, (np.array(lens) + 31) // 32)
+    length, q, dropped = spans(plan, int(tiles.sum()) * Hkv, 16)
+    if plan.compute_units == 256:
+        assert q == want and not dropped
+        at = np.concatenate([[0], np.cumsum(length)])
+        inner = {at[plan.first_light_ctx_wavefront], at[plan.first_light_ctx_wavefront + plan.num_light_ctx_wavefronts]}
+        assert inner - set(np.cumsum(np.repeat(tiles, Hkv)))           # a border inside an item
+    cfg = W.AttnConfig(name="lc", batch=B, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, sys_len=s, ctx_lo=max(lens),
+                       ctx_hi=max(lens), block_size=16)
+    case = W.make_case(cfg, 80 + s)
+    case.context_lens[:] = lens
+    pad = np.full((B, -(-bound // 16) - case.block_tables.shape[1]), W.POISON_BLOCK, np.int32)
+    case.block_tables = np.ascontiguousarray(np.concatenate([case.block_tables, pad], 1))
+    print("[case] %s lens %s slots %d" % (cfg, lens, plan.num_ctx_slots), flush=True)
+    want_o, want_l, _ = oracle.decode_attention(case.q, case.k_sys, case.v_sys, case.k_cache, case.v_cache,
+                                                case.block_tables, case.context_lens, case.scale)
+    got, lse = DeviceCase(case).decode(max_context_len=bound)
+    assert np.isfinite(got).all() and np.abs(got - want_o).max() <= 2e-3 and np.abs(lse - want_l).max() <= 1e-3
