@@ -643,10 +643,11 @@ __device__ __forceinline__ void run_context_wave(const TileArgs &a, unsigned cha
     int slot = 0;
     if (j > 0) {
         const uint32_t item_first = x0 - j;
-        uint32_t first_wave;
-        if (item_first < before_light) first_wave = class_wave(item_first, h_per_wg, h_extra, h_fix);
-        else if (item_first < before_light + l_total) first_wave = lb + class_wave(item_first - before_light, l_per_wg, 0u, l_fix);
-        else first_wave = nl + class_wave(item_first - l_total, h_per_wg, h_extra, h_fix);
+        const bool in_light = item_first >= before_light && item_first < before_light + l_total;
+        const bool behind = item_first >= before_light + l_total;                  // (of the light wavefronts)
+        const uint32_t y = in_light ? item_first - before_light : behind ? item_first - l_total : item_first;
+        const uint32_t first_wave = (in_light ? lb : behind ? nl : 0u) +
+                                    class_wave(y, in_light ? l_per_wg : h_per_wg, in_light ? 0u : h_extra, in_light ? l_fix : h_fix);
         slot = (int)(uw - first_wave);
     }
 
