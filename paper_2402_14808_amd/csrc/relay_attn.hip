@@ -175,8 +175,9 @@ PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx) {
     const double mean_new = (double)total_q / batch;
     double held = (double)p->num_blocks * p->block_size;
     if (held < total_q) held = (double)batch * max_ctx;
-    const double ctx_most = held < max_ctx ? held : max_ctx;
     const double ctx = held / batch < 0.85 * max_ctx ? held / batch : 0.85 * max_ctx;
+    double ctx_most = held < max_ctx ? held : max_ctx;      // (four times the mean: the longest of most batches)
+    if (ctx_most > 4 * held / batch) ctx_most = 4 * held / batch;
     // items per context part: blocks of 128 stacked rows of an average request, times kv heads and requests
     const int64_t ctx_base = batch * hkv * (((total_q + batch - 1) / batch * G + 127) / 128);
     const double steps = ((double)base * s + ctx_base * ctx) / 64;
@@ -215,14 +216,17 @@ PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx) {
     // with a short prompt, where the partials and the fusion launch weigh more than that walk (measured:
     // 256 requests of 4 .. 12 tokens at s = 512 145 against 162 us, 512 requests of 4 tokens at
     // s = 1024 80 against 114 us; 128 requests of 16 tokens at s = 4096 328 against 311 us) -- unless
-    // an item's walk of more than 2048 positions is what the launch would wait for (2
-    // requests of 300 .. 1000 tokens behind contexts of 3000 .. 8000: 323 us whole, 216 .. 225 cut).
+    // an item's walk of more than 2048 positions is what the launch would wait for (2 requests of 300 ..
+    // 1000 tokens behind contexts of 3000 .. 8000: 293 us whole, 178 .. 207 cut), by the bound, so that a
+    // short walk needs no estimate, and by the lengths that the cache can hold.  (Every request met costs an
+    // item 2 us beside its positions: 5 of 15 .. 28 tokens, 8 heads, s = 281, 29 us whole, 17 cut.)
     const bool few_blocks = (400 + base / 2) / base > 1 && s > 512;
     const double met = mean_new > 0 ? 128.0 / G / mean_new + 1 : 1;     // requests with rows in a block
     const double reqs = met < batch ? met : batch;
     const double walk = s + (reqs * ctx_most < held ? reqs * ctx_most : held), walk_mean = s + reqs * ctx;
     best.whole = !few_blocks && many_new_tokens(p, total_q) &&
-                 (walk <= 2048 || launch_us(walk / 64, walk_mean / 64 * base, (double)base) <= best_us);
+                 (s + reqs * max_ctx <= 2048 ||
+                  launch_us(walk / 64, walk_mean / 64 * base, (double)base) + 4 + 2 * reqs <= best_us);
     if (best.whole) best.chunk = (int)((s + 127) / 128 * 128), best.part = longest;
     if (best.chunk < 128) best.chunk = 128;
     return best;

@@ -59,3 +59,21 @@ def test_new_conversations_under_a_loose_bound_stay_one_launch(bound):
     assert untouched, "the one-launch form was expected (workspace untouched)"
     r = (rows[:, 0], rows[:, 1])
     assert np.isfinite(got).all() and np.abs(got[r] - want).max() <= TOL and np.abs(lse[r] - wlse).max() <= LSE_TOL
+
+
+
+def test_few_tokens_of_several_requests_in_a_block_are_cut():
+    """Eight blocks of rows that would go through five requests each, one after the other, under a loose bound."""
+    cfg = W.AttnConfig(name="ft", batch=5, num_q_heads=8, num_kv_heads=8, head_dim=128, sys_len=281, ctx_lo=0, ctx_hi=0,
+                       block_size=16, q_lo=15, q_hi=28)
+    case = W.make_case(cfg, 760, prefill=True)
+    pad = np.full((5, 42 - case.block_tables.shape[1]), W.POISON_BLOCK, np.int32)
+    case.block_tables = np.ascontiguousarray(np.concatenate([case.block_tables, pad], 1))
+    print("[case] %s m=%s" % (cfg, np.diff(case.cu_seqlens_q)), flush=True)
+    want, wlse, _ = oracle.prefill_attention(case.q, case.cu_seqlens_q, case.k_sys, case.v_sys, case.k_cache, case.v_cache,
+                                             case.block_tables, case.context_lens, case.scale)
+    dc = DeviceCase(case)
+    got, lse = dc.prefill(max_context_len=672)
+    untouched = bool((dc.last_workspace == 0xFF).all())
+    assert not untouched, "the cut form was expected (partials in the workspace)"
+    assert np.isfinite(got).all() and np.abs(got - want).max() <= TOL and np.abs(lse - wlse).max() <= LSE_TOL
