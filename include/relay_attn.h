@@ -235,20 +235,25 @@ ra_status relay_attn_debug_timeline(const ra_params *p,
  *   takes Q_v / 4 + (k < Q_v mod 4) of them; otherwise every wavefront takes `floor` tiles and the
  *   last ones none.
  *   Without light wavefronts all wavefronts are one class and R = N.
- *   With light wavefronts (numbers first_light_ctx_wavefront .. + num_light_ctx_wavefronts - 1:
- *   the ones that share a compute unit with a system workgroup, which is known when the launch
- *   is exactly two workgroups per compute unit) every light workgroup takes
+ *   Light wavefronts are numbers first_light_ctx_wavefront .. + num_light_ctx_wavefronts - 1: the ones
+ *   that share a compute unit with a system workgroup, which is known for the workgroups that a launch
+ *   of at least two per compute unit starts with.  The others are "heavy".
+ *   Launches of exactly two workgroups per compute unit: every light workgroup takes
  *   L = (sys_tiles_total + N) / 256 - sys_workgroup_tiles tiles (0 if that is negative), split over
- *   its four wavefronts as above; if L / 4 < floor its first q wavefronts take floor tiles each and the
- *   others none, q = 0 .. 4 being the least number (with no more than N tiles in all) that makes the
- *   larger of sys_workgroup_tiles + q floor and 2 ((N - tiles of the light ones) / heavy workgroups)
- *   least.  No light wavefront takes any if together they would exceed N.  The other ("heavy") wavefronts are a class that shares the rest, so that every
- *   compute unit ends up with about the same number of tiles.  Should a span of either class then
- *   exceed (max_blocks_per_span - 1) * block_size / 32 tiles, the split into light and heavy is
- *   dropped.  Wavefronts whose span is empty do not count when segments of an item are numbered.
- * Every output row then has num_sys_chunks + num_ctx_slots partial results for the relay fusion
- * (Eq. 7 in n-partial form); a context item never spans more than num_ctx_slots wavefronts, and a
- * wavefront's span inside one item never covers more than max_blocks_per_span cache blocks.
+ *   its four wavefronts as above; if L / 4 < floor its first q wavefronts take floor tiles each and
+ *   the others none, q = 0 .. 4 being the least number (with no more than N tiles in all) that makes
+ *   the larger of sys_workgroup_tiles + q floor and 2 ((N - tiles of the light ones) / heavy
+ *   workgroups) least.  No light wavefront takes any if together they would exceed N.  The heavy
+ *   wavefronts are a class that shares the rest, so that every compute unit ends up with about the
+ *   same number of tiles.  Should a span of either class then exceed
+ *   (max_blocks_per_span - 1) * block_size / 32 tiles, the split into light and heavy is dropped.
+ *   Larger launches: the light wavefronts take none if N <= floor * heavy wavefronts; otherwise there
+ *   is no such split.
+ *   Wavefronts whose span is empty do not count when segments of an item are numbered.
+ * Every output row then has at most num_sys_chunks + num_ctx_slots partial results for the relay
+ * fusion (Eq. 7 in n-partial form): one per system chunk and one per span its context meets.  A
+ * context item never meets more than num_ctx_slots spans, and a span inside one item never covers
+ * more than max_blocks_per_span cache blocks.
  *   sys_rows_per_workgroup is 32 (a row tile streams its chunk alone) or, for batches with many
  *   stacked rows B * num_q_heads / num_kv_heads per kv head (from 128 on, depending on how the
  *   system part compares with the context part) and one shared prefix, 128

@@ -62,7 +62,8 @@ struct TileArgs {                // both partial attentions of a decode step in 
     int ctx_waves, ctx_t_floor, n_ctx_slots, max_ctx;
     int ctx_t_cap;               // most tiles a span may have (its block ids must fit the LDS table)
     // context wavefronts that share a compute unit with a system workgroup (0: none known), the
-    // tiles of such a system workgroup, and the tiles of all system workgroups together
+    // tiles of such a system workgroup, and the tiles of all system workgroups together (0: a launch
+    // of more than two workgroups per compute unit, where light wavefronts only ever take nothing)
     int ctx_light_begin, ctx_light_waves, sys_wg_tiles, sys_tiles_total;
     int block_size_log2, max_blocks_per_seq, rows;
     int sys_head_fastest;        // system item order: kv head varies fastest (token-major cache)

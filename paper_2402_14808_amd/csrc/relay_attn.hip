@@ -471,6 +471,13 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
     return pl;
 }
 
+// Decode launches of more than two workgroups per compute unit whose system workgroups all sit on units
+// of their own: the context workgroups next to them are the last that should get work.
+bool light_if_spare(int64_t sys_wgs, int64_t ctx_wgs) {
+    const int cus = device_compute_units();
+    return cus == kReferenceCus && sys_wgs > 0 && sys_wgs <= cus && sys_wgs + ctx_wgs > 2 * cus;
+}
+
 // Where the partial-attention launch records the begin and end of its wavefronts (measurement aid).
 struct Timeline {
     unsigned long long *entries = nullptr;   // device, 2 per wavefront
@@ -707,6 +714,11 @@ ra_status run(const ra_params *p, const void *q, const int32_t *cu_seqlens_q, in
                        (pl.rows_sys ? pl.n_sys_rowblocks : ceil_div(prefixes[i].num_requests * pl.group, 32)) *
                        ceil_div(prefixes[i].sys_len, 32);
             t.sys_tiles_total = (int)(sum > INT32_MAX / 2 ? INT32_MAX / 2 : sum);
+        } else if (light_if_spare(items, pl.ctx_wgs)) {
+            t.ctx_light_begin = (kWorkgroupSlots / 2 - items) * 4;
+            t.ctx_light_waves = items * 4;
+            t.sys_wg_tiles = INT32_MAX / 2;             // (more than any unit: no light span)
+            t.sys_tiles_total = 0;
         }
         t.block_size_log2 = pl.block_size_log2;
         t.max_blocks_per_seq = p->max_blocks_per_seq;
@@ -817,6 +829,9 @@ ra_status relay_attn_decode_plan(const ra_params *p, ra_decode_plan *plan) {
                             ceil_div(p->sys_len, 32);
     if (pl.paired && plan->num_sys_workgroups + pl.ctx_wgs == kWorkgroupSlots &&
         plan->num_sys_workgroups <= kWorkgroupSlots / 2) {
+        plan->first_light_ctx_wavefront = (kWorkgroupSlots / 2 - plan->num_sys_workgroups) * 4;
+        plan->num_light_ctx_wavefronts = plan->num_sys_workgroups * 4;
+    } else if (light_if_spare(plan->num_sys_workgroups, pl.ctx_wgs)) {
         plan->first_light_ctx_wavefront = (kWorkgroupSlots / 2 - plan->num_sys_workgroups) * 4;
         plan->num_light_ctx_wavefronts = plan->num_sys_workgroups * 4;
     }

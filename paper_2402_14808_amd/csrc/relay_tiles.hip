@@ -485,6 +485,10 @@ __device__ __forceinline__ int wave_inclusive_scan(int x, int lane) {
 // so the context workgroups that sit next to a system workgroup ("light") get spans that bring
 // their unit up to the average, and the ones that sit next to each other ("heavy") share the
 // rest.  ctx_light_begin .. + ctx_light_waves are the light wavefronts; none: all spans equal.
+// Larger launches (a bound far above the lengths) start the same way: there (sys_tiles_total 0) the
+// light wavefronts take nothing where the others can take all tiles at the floor, and all spans are
+// equal otherwise.  60 requests of 32/8 heads, s = 4096, contexts of 500 .. 2000 under a bound of 17392,
+// 64 system workgroups of 128 tiles: 87.8 us with work next to them, 72.4 without.
 template <int D, bool APPEND>
 __device__ __forceinline__ void run_context_wave(const TileArgs &a, unsigned char *smem,
                                                  float (*sm_m)[32], float (*sm_l)[32],
@@ -517,7 +521,7 @@ __device__ __forceinline__ void run_context_wave(const TileArgs &a, unsigned cha
     uint32_t lb = (uint32_t)a.ctx_light_begin, nl = (uint32_t)a.ctx_light_waves;
     const uint32_t n_heavy = (uint32_t)a.ctx_waves - nl;
     uint32_t l_per_wg = 0, l_fix = 0, l_total = 0, l_q = kWaves;
-    if (nl > 0 && n_heavy > 0) {
+    if (nl > 0 && n_heavy > 0 && (a.sys_tiles_total > 0 || n_tiles <= n_heavy * floor_t)) {
         // tiles per compute unit, and what a system workgroup leaves of it for its neighbour
         const uint32_t per_unit = ((uint32_t)a.sys_tiles_total + n_tiles) / 256u;
         const uint32_t l4 = per_unit > (uint32_t)a.sys_wg_tiles ? per_unit - (uint32_t)a.sys_wg_tiles : 0;

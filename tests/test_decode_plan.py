@@ -38,6 +38,11 @@ def spans(plan, N, bs):
     lb, nl = plan.first_light_ctx_wavefront, plan.num_light_ctx_wavefronts
     if nl == 0 or W == nl:
         return shared(N, W // 4), None, False
+    if plan.num_sys_workgroups + W // 4 > 2 * plan.compute_units:
+        if N > floor * (W - nl):
+            return shared(N, W // 4), None, False
+        heavy = shared(N, (W - nl) // 4)
+        return heavy[:lb] + [0] * nl + heavy[lb:], "spare", False
     l4 = max((plan.sys_tiles_total + N) // 256 - plan.sys_workgroup_tiles, 0)
     heavy_wgs, q = (W - nl) // 4, None
     if l4 // 4 >= floor:
@@ -163,11 +168,11 @@ def _check_cover(plan, lens, Hkv, bs):
 
 
 def test_every_way_the_light_wavefronts_come_out_covers_the_tiles():
-    """Launches of exactly two workgroups per compute unit over lengths from empty to the bound: an even share
-    of the light wavefronts, q = 0 .. 4 of four with a span, and the split dropped for spans that would not
-    fit the block table, each met at least once."""
+    """Launches with light wavefronts over lengths from empty to the bound: an even share of them, q = 0 .. 4 of
+    four with a span, none in a larger launch, and the split dropped for spans that would not fit the
+    block table, each met at least once."""
     rng = np.random.Generator(np.random.PCG64(4))
-    seen = dict.fromkeys(("even", 0, 1, 2, 3, 4, "dropped"), 0)
+    seen = dict.fromkeys(("even", 0, 1, 2, 3, 4, "spare", "dropped"), 0)
     for _ in range(4000):
         G = int(rng.choice([1, 1, 2, 4, 7]))
         Hkv = int(rng.choice([1, 2, 4, 8, 16, 32, 40, 52]))

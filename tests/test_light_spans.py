@@ -47,6 +47,30 @@ def test_decode_matches_oracle(B, H, s, bound, ctx, want):
     assert np.isfinite(got).all() and np.abs(got[r] - want_o).max() <= 2e-3 and np.abs(lse[r] - want_l).max() <= 1e-3
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,Hq,Hkv,d,s,bound,ctx", [
+    (58, 16, 4, 64, 101, 438, (200, 400)),       # spans of one item on both sides of the gap
+    (17, 64, 16, 128, 117, 378, (180, 378)),
+    (60, 8, 4, 64, 1000, 40000, (0, 400)),       # all work in front of the gap
+])
+def test_larger_launches_that_leave_the_light_ones_out_match_oracle(B, Hq, Hkv, d, s, bound, ctx):
+    plan = ra.relay_attn_decode_plan(_params(B, Hq, Hkv, s, bound, d=d))
+    cfg = W.AttnConfig(name="lo", batch=B, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, sys_len=s, ctx_lo=ctx[0],
+                       ctx_hi=ctx[1], block_size=16)
+    case = W.make_case(cfg, 90 + d)
+    n_tiles = int(np.maximum(1, (case.context_lens + 31) // 32).sum()) * Hkv
+    length, q, _ = spans(plan, n_tiles, 16)
+    if plan.compute_units == 256:
+        assert q == "spare" and (sum(length[:plan.first_light_ctx_wavefront]) < n_tiles) == (bound < 1000)
+    pad = np.full((B, -(-bound // 16) - case.block_tables.shape[1]), W.POISON_BLOCK, np.int32)
+    case.block_tables = np.ascontiguousarray(np.concatenate([case.block_tables, pad], 1))
+    print("[case] %s slots %d" % (cfg, plan.num_ctx_slots), flush=True)
+    want_o, want_l, _ = oracle.decode_attention(case.q, case.k_sys, case.v_sys, case.k_cache, case.v_cache,
+                                                case.block_tables, case.context_lens, case.scale)
+    got, lse = DeviceCase(case).decode(max_context_len=bound)
+    assert np.isfinite(got).all() and np.abs(got - want_o).max() <= 2e-3 and np.abs(lse - want_l).max() <= 1e-3
+
+
 # contexts whose items run from heavy wavefronts into light ones, out of them, or through all of them
 @pytest.mark.gpu
 @pytest.mark.parametrize("Hq,Hkv,s,bound,lens,want", [
