@@ -351,23 +351,23 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
                 if (base_items * n_chunks > kWorkgroupSlots / 2) n_chunks = kWorkgroupSlots / 2 / base_items;
                 if (n_chunks < 1) n_chunks = 1;
                 chunk = (int)((sys_tiles + n_chunks - 1) / n_chunks) * 32;
-                // Small launches (up to 2.5 tiles per wavefront) wait for their longest chain of tiles, 2 - 3 us
-                // each, and for units that got two workgroups where most got one; the four wavefronts
-                // take a chunk's tiles in turn.  So the chunk becomes a multiple of four tiles:
-                // the next lower one where that saves one of three or more turns and leaves half of the
-                // units without a system workgroup (one request of 16 heads at s = 1625, 11 -> 8 tiles,
-                // 19.5 -> 16.5 us; on more units 12.3 -> 14.1, 88 requests of 16 heads at 787), or the next
-                // higher one, as many turns, where that brings the launch from just above one
-                // workgroup per unit down to it (two requests of 32 heads at 3221, 280 -> 248 workgroups,
-                // 20.4 -> 17.7 us; without that effect 13.4 -> 14.0, 10 requests of 28/4 heads at 1989).
-                const int64_t tiles = chunk / 32, down = tiles / 4 * 4, up = down + 4;
-                if (!tight && t_star16 <= 40 && tiles > 4 && down < tiles) {
+                // Small launches (up to 2.5 tiles per wavefront) wait for units that got two workgroups
+                // where most got one.  The four wavefronts take a chunk's tiles in turn, so up to the next
+                // multiple of four a longer chunk takes as many turns; it is taken where it brings
+                // the launch from above one workgroup per unit (by a quarter at most: beyond that the
+                // second ones are spread anyway) down to it.  Both sides of 40 such launches, 1 .. 59
+                // requests: 0.83 .. 1.00 of the time on 38 (two requests of 32 heads, s = 4152, 24.1 -> 19.9
+                // us), 1.04 and 1.05 on two; without that effect 13.4 -> 14.0 (10 requests of 28/4 heads, s =
+                // 1989).  Up to four tiles are one turn as they are.  (A multiple of four below, a turn
+                // less, gives the context side shorter spans as well and was slower on 74 launches of 111,
+                // by up to 21 %.)
+                const int64_t tiles = chunk / 32, up = tiles / 4 * 4 + 4;
+                if (t_star16 <= 40 && tiles > 4 && tiles % 4 != 0) {
                     const int64_t like16 = up * 4 > t_star16 ? up * 4 : t_star16;
                     const int64_t units = kWorkgroupSlots / 2, ctx_like = (ctx_tiles * 16 + 4 * like16 - 1) / (4 * like16);
                     auto wgs_at = [&](int64_t t) { return base_items * ((sys_tiles + t - 1) / t); };
                     const int64_t total = wgs_at(tiles) + ctx_like;
-                    if (tiles > 8 && (sys_tiles + down - 1) / down <= 8 && wgs_at(down) <= units / 2) chunk = (int)down * 32;
-                    else if (total > units && total <= units * 5 / 4 && wgs_at(up) + ctx_like <= units) chunk = (int)up * 32;
+                    if (total > units && total <= units * 5 / 4 && wgs_at(up) + ctx_like <= units) chunk = (int)up * 32;
                 }
             }
             pl.sys_chunk = chunk;

@@ -10,11 +10,21 @@ from test_decode_plan import _params
 
 # batch, q heads, kv heads, head_dim, prompt, bound, tiles of a chunk
 CASES = [
-    (1, 16, 16, 64, 1625, 8140, 8),        # a turn less: 11 tiles without the rule
+    (1, 16, 16, 64, 1625, 8140, 11),       # not one workgroup per unit either way: stays (8, a turn less, was no faster)
     (2, 32, 32, 128, 3221, 188, 16),       # 13: one workgroup per unit instead of a few more
     (12, 32, 8, 128, 6612, 46, 16),        # 13, stacked rows of a grouped model
     (88, 16, 16, 64, 787, 35, 9),          # half of the units would hold a system workgroup: stays
     (1, 4, 4, 64, 96, 64, 3),              # up to four tiles: stays
+    # either side of a limit: workgroups without the rule, 256 per launch of one per unit
+    (8, 32, 32, 128, 185, 201, 6),         # 256: fits as it is
+    (1, 16, 16, 64, 7646, 20, 16),         # 257, 241 with a chunk of 16
+    (12, 32, 8, 128, 4119, 308, 12),       # 320, a quarter more: 256
+    (1, 32, 32, 128, 477, 1531, 8),        # 288: 256
+    (22, 32, 8, 64, 2616, 171, 9),         # 328, more than a quarter: stays
+    (1, 32, 8, 128, 6159, 1820, 7),        # 281: 257 with a chunk of 8
+    # 2.5 tiles per wavefront, and a little more
+    (4, 40, 40, 128, 3140, 206, 20),
+    (1, 16, 16, 64, 10363, 22, 21),
 ]
 
 
