@@ -599,23 +599,25 @@ __device__ __forceinline__ void run_context_wave(const TileArgs &a, unsigned cha
         const uint32_t q = per_wg + (v < extra ? 1u : 0u);
         return v * per_wg + min(v, extra) + k * (q >> 2) + min(k, q & 3u);
     };
-    // the wavefront of a class whose span holds tile y of the class
+    // the wavefront of a class whose span holds tile y of the class (workgroups of per_wg + 1 tiles come
+    // first, and in a workgroup of q tiles wavefronts of q / 4 + 1)
     auto class_wave = [](uint32_t y, uint32_t per_wg, uint32_t extra, uint32_t fix) -> uint32_t {
         if (fix > 0) return y / fix;
-        const uint32_t longer = extra * (per_wg + 1u);                             // tiles of the workgroups that take one more
-        const uint32_t v = y < longer ? y / (per_wg + 1u) : extra + (y - longer) / per_wg;
-        const uint32_t q = per_wg + (v < extra ? 1u : 0u), r = y - (v * per_wg + min(v, extra));
-        const uint32_t short_len = q >> 2, first = (q & 3u) * (short_len + 1u);
-        return 4u * v + (r < first ? r / (short_len + 1u) : (q & 3u) + (r - first) / short_len);
+        const uint32_t longer = extra * (per_wg + 1u);
+        const bool in_longer = y < longer;
+        const uint32_t q = per_wg + (in_longer ? 1u : 0u), from = in_longer ? y : y - longer, v = from / q, r = from - v * q;
+        const uint32_t first = (q & 3u) * ((q >> 2) + 1u);
+        const bool in_first = r < first;
+        const uint32_t k = (in_first ? r : r - first) / ((q >> 2) + (in_first ? 1u : 0u));
+        return 4u * (v + (in_longer ? 0u : extra)) + k + (in_first ? 0u : q & 3u);
     };
     auto len_of_wave = [=](uint32_t u) -> uint32_t {
         if (u >= lb && u < lb + nl) return class_len(u - lb, l_per_wg, 0u, l_fix);
         return class_len(u < lb ? u : u - nl, h_per_wg, h_extra, h_fix);
     };
     uint32_t x0;
-    const uint32_t before_light = class_first(lb, h_per_wg, h_extra, h_fix);       // tiles of the heavy wavefronts below lb
     if (uw < lb) x0 = class_first(uw, h_per_wg, h_extra, h_fix);
-    else if (uw < lb + nl) x0 = before_light + class_first(uw - lb, l_per_wg, 0u, l_fix);
+    else if (uw < lb + nl) x0 = class_first(lb, h_per_wg, h_extra, h_fix) + class_first(uw - lb, l_per_wg, 0u, l_fix);
     else x0 = class_first(uw - nl, h_per_wg, h_extra, h_fix) + l_total;
     const uint32_t my_len = len_of_wave(uw);
     if (x0 >= n_tiles || my_len == 0) return;
@@ -647,6 +649,8 @@ __device__ __forceinline__ void run_context_wave(const TileArgs &a, unsigned cha
     int slot = 0;
     if (j > 0) {
         const uint32_t item_first = x0 - j;
+        // tiles of the heavy wavefronts below the light ones
+        const uint32_t before_light = nl > 0 ? class_first(lb, h_per_wg, h_extra, h_fix) : n_tiles;
         const bool in_light = item_first >= before_light && item_first < before_light + l_total;
         const bool behind = item_first >= before_light + l_total;                  // (of the light wavefronts)
         const uint32_t y = in_light ? item_first - before_light : behind ? item_first - l_total : item_first;
