@@ -85,7 +85,8 @@ typedef struct {
     int32_t head_dim;             /* 64 or 128                                           */
     int32_t sys_len;              /* s >= 0 shared system positions                      */
     int32_t block_size;           /* tokens per cache block: 8, 16, 32, ... (power of 2) */
-    int32_t num_blocks;           /* blocks in k_cache / v_cache                         */
+    int32_t num_blocks;           /* blocks in k_cache / v_cache (the prompt phase also goes by
+                                     them where it weighs how long contexts can be)      */
     int32_t max_blocks_per_seq;   /* row length of block_tables                          */
     int32_t max_context_len;      /* host-side upper bound on context_lens[i]; 0 means
                                      max_blocks_per_seq * block_size.  Lengths above it
@@ -168,10 +169,13 @@ ra_status relay_attn_decode_append(const ra_params *p,
  * fixed array inside the library's device code instead (relay_attn_static_scratch_bytes() =
  * 32 MiB; every GPU the library runs on holds its copy until the process ends; its address is
  * looked up on the first call on a device).  Nothing is allocated, freed or copied.
- *   - A call whose partials would not fit returns RA_ERR_WORKSPACE_TOO_SMALL before any launch
- *     (the need is relay_attn_workspace_bytes(p, batch): about 0.5 KiB x output rows x partials
- *     per row; the Llama-30B shape at batch 32 needs 7 MiB, the Llama-3-8B shape at batch 128
- *     28 MiB).
+ *   - A call whose partials would not fit returns RA_ERR_WORKSPACE_TOO_SMALL before any launch.  The
+ *     need is that of the decode plan alone, (head_dim + 1) * 4 bytes x output rows x
+ *     (num_sys_chunks + num_ctx_slots) of relay_attn_decode_plan: 4.1 MiB for the Llama-30B shape at
+ *     batch 32, 30.2 MiB for the Llama-3-8B shape at batch 128, s = 8192, contexts up to 1024.
+ *     (relay_attn_workspace_bytes covers every entry point and may be larger than the array for a
+ *     call that fits.)  Slots that a call can do without are left out where the array would not hold
+ *     them.
  *   - The array needs no clearing between calls: every slot a call reads it has written itself.
  *   - All calls on one GPU share the one array: calls that overlap in time on the same GPU
  *     (two streams, two threads) race and must not be made; use relay_attn_decode with a
@@ -337,11 +341,12 @@ ra_status relay_attn_decode_grouped(const ra_params *p,
  * (context_lens[i] >= m_i): new token j attends to all system positions and
  * to context positions 0 .. context_lens[i]-m_i+j (causal).  out / lse_out are
  * indexed by packed token.
- * The workspace is required as for the decode step (relay_attn_workspace_bytes(p, total_q)); a
- * call with at least 32 new tokens per request on average (4 when the system prompt has at most
- * 1024 positions), a system prompt that is one chunk of work, contexts that are not what the launch
- * would wait for and no hand-set p->sys_chunk_tokens / ctx_part_tokens runs as a single launch that does
- * not touch it (the relay fusion of Alg. 1 happens in the accumulators), other calls write
+ * The workspace is required as for the decode step (relay_attn_workspace_bytes(p, total_q)).  A
+ * call runs as a single launch that does not touch it (the relay fusion of Alg. 1 happens in the
+ * accumulators) if it brings at least 32 new tokens per request on average (4 when the system
+ * prompt has at most 1024 positions), its system prompt is one chunk of work, contexts are not what
+ * the launch would wait for (by max_context_len and by what num_blocks can hold) and
+ * p->sys_chunk_tokens / ctx_part_tokens are not set by hand; other calls write
  * partials there and fuse them in a second launch.  The results agree within the tolerance, not
  * bit for bit, between the two forms.
  */

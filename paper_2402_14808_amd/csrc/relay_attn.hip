@@ -153,11 +153,11 @@ PromptSplit coarse_split(const ra_params *p, int32_t total_q) {
 // A prompt-phase launch takes about as long as the larger of its longest item and its work per
 // compute unit, plus the thin end of the launch; a finer cut shortens the first and the last
 // of these and costs partials, which are written, read again and fused.  The estimate below was
-// fitted to 570 measured cuts of 16 shapes (system prompts of 300 .. 12000, contexts up to 8000, 80 ..
-// 14400 stacked rows per kv head, 4 .. 40 kv heads, head_dim 64 and 128): its choice took within 3 % of the
-// best cut of each shape on most and 13 % at worst, against up to 3.5 times for the fixed rule in front of it
-// (chunks of 512 or more, one context part of 4096 positions): 8 requests of 9 .. 75 tokens behind
-// contexts of 300 .. 4000 118 -> 75 us, 4 requests of 10 .. 100 tokens behind 500 .. 2000 132 -> 38 us.
+// fitted to measured cuts of 16 shapes (system prompts of 300 .. 12000, contexts up to 8000, 80 .. 14400
+// stacked rows per kv head, 4 .. 40 kv heads, head_dim 64 and 128).  Over 478 cuts of 21 shapes, taken again
+// with the present item order, its choice is 1 .. 12 % over the best cut of a shape, against up to 3.5 times for
+// the fixed rule in front of it (coarse_split): 8 requests of 9 .. 75 tokens behind contexts of 300 ..
+// 4000 118 -> 67 us, 4 requests of 10 .. 100 tokens behind 500 .. 2000 132 -> 37 us.
 // Uses nothing that the workspace size is not computed from.
 PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx) {
     const int64_t G = p->num_q_heads / p->num_kv_heads, hkv = p->num_kv_heads, batch = p->batch > 0 ? p->batch : 1;

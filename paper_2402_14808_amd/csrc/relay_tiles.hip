@@ -605,7 +605,8 @@ __device__ __forceinline__ void run_context_wave(const TileArgs &a, unsigned cha
         if (fix > 0) return y / fix;
         const uint32_t longer = extra * (per_wg + 1u);
         const bool in_longer = y < longer;
-        const uint32_t q = per_wg + (in_longer ? 1u : 0u), from = in_longer ? y : y - longer, v = from / q, r = from - v * q;
+        const uint32_t q = per_wg + (in_longer ? 1u : 0u), from = in_longer ? y : y - longer;
+        const uint32_t v = from / q, r = from - v * q;
         const uint32_t first = (q & 3u) * ((q >> 2) + 1u);
         const bool in_first = r < first;
         const uint32_t k = (in_first ? r : r - first) / ((q >> 2) + (in_first ? 1u : 0u));
@@ -654,9 +655,9 @@ __device__ __forceinline__ void run_context_wave(const TileArgs &a, unsigned cha
         const bool in_light = item_first >= before_light && item_first < before_light + l_total;
         const bool behind = item_first >= before_light + l_total;                  // (of the light wavefronts)
         const uint32_t y = in_light ? item_first - before_light : behind ? item_first - l_total : item_first;
-        const uint32_t first_wave = (in_light ? lb : behind ? nl : 0u) +
-                                    class_wave(y, in_light ? l_per_wg : h_per_wg, in_light ? 0u : h_extra, in_light ? l_fix : h_fix);
-        slot = (int)(uw - first_wave);
+        const uint32_t before_class = in_light ? lb : behind ? nl : 0u;
+        slot = (int)(uw - before_class -
+                     class_wave(y, in_light ? l_per_wg : h_per_wg, in_light ? 0u : h_extra, in_light ? l_fix : h_fix));
     }
 
     uint32_t x = x0;
