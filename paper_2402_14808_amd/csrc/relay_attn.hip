@@ -634,16 +634,23 @@ ra_status run(const ra_params *p, const void *q, const int32_t *cu_seqlens_q, in
             if (r.n_ctx_parts < 1 || r.ctx_part < 1) r.n_ctx_parts = 0, r.ctx_part = 1;   // no context at all
         }
         if (num_prefixes > 1) {                    // system items prefix by prefix
-            int items = 0;
+            int by_len[ra::kMaxPrefixes];          // the longest first: their items are what the launch would wait for
             for (int i = 0; i < num_prefixes; ++i) {
+                int at = i;
+                for (; whole && at > 0 && prefixes[by_len[at - 1]].sys_len < prefixes[i].sys_len; --at) by_len[at] = by_len[at - 1];
+                by_len[at] = i;
+            }
+            int items = 0;
+            for (int at = 0; at < num_prefixes; ++at) {
+                const int i = by_len[at];
                 items += p->num_kv_heads * ceil_div(ntok[i] * pl.group, 128) *
                          (whole ? 1 : pl.sys_chunk > 0 ? ceil_div(prefixes[i].sys_len, pl.sys_chunk) : 0);
-                r.pfx_item_end[i] = items;
-                r.pfx_tok0[i] = tok0[i];
-                r.pfx_ntok[i] = ntok[i];
-                r.pfx_len[i] = prefixes[i].sys_len;
-                r.pfx_k[i] = static_cast<const uint16_t *>(prefixes[i].k_sys);
-                r.pfx_v[i] = static_cast<const uint16_t *>(prefixes[i].v_sys);
+                r.pfx_item_end[at] = items;
+                r.pfx_tok0[at] = tok0[i];
+                r.pfx_ntok[at] = ntok[i];
+                r.pfx_len[at] = prefixes[i].sys_len;
+                r.pfx_k[at] = static_cast<const uint16_t *>(prefixes[i].k_sys);
+                r.pfx_v[at] = static_cast<const uint16_t *>(prefixes[i].v_sys);
             }
             r.n_sys_items = items;
         }

@@ -1,0 +1,25 @@
+"""The one-launch prompt phase with several prefixes starts its items with the longest prompt's: any order of the
+lengths, equal and empty ones among them, gives every group its own prompt."""
+import numpy as np
+import pytest
+
+import workloads as W
+from test_gpu_multi_prefix import _prefill_oracle, _run_prefill
+
+pytestmark = pytest.mark.gpu
+TOL, LSE_TOL = 2e-3, 1e-3          # as in the other parity tests: fp32 output, error about 1e-6
+
+
+@pytest.mark.parametrize("lens", [(40, 90, 200, 200), (200, 0, 90, 40), (90, 200, 0, 90), (1, 64, 65, 129)])
+@pytest.mark.parametrize("d,Hq,Hkv", [(128, 4, 1), (64, 3, 3)])
+def test_any_order_of_prompt_lengths(lens, d, Hq, Hkv):
+    cfg = W.AttnConfig(name="po", batch=6, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, sys_len=max(lens), ctx_lo=0,
+                       ctx_hi=40, block_size=16, q_lo=33, q_hi=70)
+    case = W.make_case(cfg, 770 + lens[0], prefill=True, extra_context=True)
+    groups = W.make_prefix_groups(case, 771, (1, 2, 2, 1), lens)
+    print("[case] %s lens %s m=%s" % (cfg, lens, np.diff(case.cu_seqlens_q)), flush=True)
+    got, lse = _run_prefill(case, groups)
+    untouched = bool((_run_prefill.last_workspace == 0xFF).all())
+    assert untouched, "the one-launch form was expected"
+    want, wlse = _prefill_oracle(case, groups)
+    assert np.isfinite(got).all() and np.abs(got - want).max() <= TOL and np.abs(lse - wlse).max() <= LSE_TOL
