@@ -159,7 +159,7 @@ PromptSplit coarse_split(const ra_params *p, int32_t total_q) {
 // the fixed rule in front of it (coarse_split): 8 requests of 9 .. 75 tokens behind contexts of 300 ..
 // 4000 118 -> 67 us, 4 requests of 10 .. 100 tokens behind 500 .. 2000 132 -> 37 us.
 // Uses nothing that the workspace size is not computed from.
-PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx) {
+PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx, int num_groups, double sys_mean) {
     const int64_t G = p->num_q_heads / p->num_kv_heads, hkv = p->num_kv_heads, batch = p->batch > 0 ? p->batch : 1;
     const int64_t s = p->sys_len, base = hkv * ((total_q * G + 127) / 128);
     const double row_bytes = (double)total_q * p->num_q_heads * p->head_dim * 4;
@@ -211,22 +211,30 @@ PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx) {
             if (us < best_us) best_us = us, best.chunk = (int)chunk, best.part = (int)part;
         }
     }
-    // Whole items: where blocks of 128 rows alone come near to filling the machine (or the prompt is
-    // too short to be cut) and a block does not meet too many requests: at least 32 new tokens per request, or 4
-    // with a short prompt, where the partials and the fusion launch weigh more than that walk (measured:
-    // 256 requests of 4 .. 12 tokens at s = 512 145 against 162 us, 512 requests of 4 tokens at
-    // s = 1024 80 against 114 us; 128 requests of 16 tokens at s = 4096 328 against 311 us) -- unless
-    // an item's walk of more than 2048 positions is what the launch would wait for (2 requests of 300 ..
-    // 1000 tokens behind contexts of 3000 .. 8000: 293 us whole, 178 .. 207 cut), by the bound, so that a
-    // short walk needs no estimate, and by the lengths that the cache can hold.  (Every request met costs an
-    // item 2 us beside its positions: 5 of 15 .. 28 tokens, 8 heads, s = 281, 29 us whole, 17 cut.)
-    const bool few_blocks = (400 + base / 2) / base > 1 && s > 512;
+    // Whole items or the cut, by an estimate of each.  Both forms of 480 drawn calls (4 .. 930 new tokens per
+    // request, 1 .. 32 requests, 4 .. 52 kv heads, prompts of 100 .. 16000) were timed; the estimate of the whole form
+    // is within 13 % of its time (one standard deviation): every request whose rows a block meets costs it a
+    // range of keys of its own, and the longest context is taken as twice the mean.  The form it picks is 1.1 %
+    // over the faster one in the mean.  The rule in front of it was 4.7 % over, and up to four times where a
+    // short walk alone decided: 17 requests of 10 .. 13 tokens, 8 heads, s = 324, 66.1 us whole, 16.0 cut; one of
+    // 57 tokens of 28/4 heads behind 1667, 57 and 20; the other way, 264 blocks of 5 prompts with s = 1726
+    // 62 us whole, 81 cut.
+    // With several prompts the requests of a block share one of them: no more meet than an average group has
+    // (the workspace is sized without the groups, so they may only ever speak for the whole form, which needs none).
     const double met = mean_new > 0 ? 128.0 / G / mean_new + 1 : 1;     // requests with rows in a block
-    const double reqs = met < batch ? met : batch;
-    const double walk = s + (reqs * ctx_most < held ? reqs * ctx_most : held), walk_mean = s + reqs * ctx;
-    best.whole = !few_blocks && many_new_tokens(p, total_q) &&
-                 (s + reqs * max_ctx <= 2048 ||
-                  launch_us(walk / 64, walk_mean / 64 * base, (double)base) + 4 + 2 * reqs <= best_us);
+    const double reqs_any = met < batch ? met : batch, group = ceil((double)batch / num_groups);
+    const double reqs = reqs_any < group ? reqs_any : group;
+    const double ctx_long = ctx_most < 2 * held / batch ? ctx_most : 2 * held / batch;
+    const double walk = ceil(s / 64.0) + reqs * ceil(ctx_long / 64), walk_mean = ceil(sys_mean / 64) + reqs * (ctx / 64 + 0.5);
+    const double blocks = base / cus, even = 0.8 * walk_mean * blocks + 0.55 * walk;
+    const double whole_us = 8.6 + (p->head_dim == 128 ? 1.42 : 0.95) * (walk > even ? walk : even) + 0.8 * reqs + 4.3 * blocks;
+    const double cut_us = 14 + (p->head_dim == 128 ? 0.85 : 0.75) * (best_us - 12);      // (as measured beside them)
+    // Few blocks with a short walk stay whole without an estimate where the requests bring 32 tokens and
+    // more: that form leaves the workspace alone (5 requests of 63 tokens, 8 heads, s = 493, 29.0 us, 19.8
+    // cut, is the most it costs).
+    const bool short_walk =
+        s <= 512 && total_q >= (int64_t)kWholeMinTokens * batch && s + reqs_any * max_ctx <= 2048 - 28 * base;
+    best.whole = many_new_tokens(p, total_q) && (short_walk || whole_us <= cut_us);
     if (best.whole) best.chunk = (int)((s + 127) / 128 * 128), best.part = longest;
     if (best.chunk < 128) best.chunk = 128;
     return best;
@@ -243,7 +251,8 @@ constexpr int kRowsSysMinTiles = 8;
 // the fewest partials: the cut that a caller's workspace of fixed size, made for another batch, may
 // still hold (the size does not only rise with the batch).
 Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q_len,
-               int64_t sys_base_items = 0, bool allow_rows_sys = true, size_t budget = SIZE_MAX) {
+               int64_t sys_base_items = 0, bool allow_rows_sys = true, size_t budget = SIZE_MAX, int num_groups = 1,
+               double sys_mean = -1) {
     Plan pl{};
     const bool tight = budget != SIZE_MAX;
     const bool prefill = kind == kPrefill;
@@ -447,7 +456,7 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
 
     const bool hand_set = p->sys_chunk_tokens != 0 || p->ctx_part_tokens != 0;
     PromptSplit split{false, 0, 256};
-    if (prefill && !hand_set && !tight) split = split_prompt(p, total_q, pl.max_ctx);
+    if (prefill && !hand_set && !tight) split = split_prompt(p, total_q, pl.max_ctx, num_groups, sys_mean < 0 ? p->sys_len : sys_mean);
     else if (p->sys_len > 0 || prefill) split = coarse_split(p, total_q);
     if (!prefill) split.part = 256;
     pl.whole = prefill && !hand_set && split.whole;
@@ -537,9 +546,11 @@ ra_status run(const ra_params *p, const void *q, const int32_t *cu_seqlens_q, in
     // need more than that, the grouping-blind one (which is what the size was computed from) is used.
     // Where the workspace is smaller than either, the cut with the fewest partials may still fit it.
     const bool multi = num_prefixes > 1;
+    double sys_mean = 0;
+    for (int i = 0; i < num_prefixes; ++i) sys_mean += (double)prefixes[i].sys_len / num_prefixes;
     Plan pl{};
     for (size_t budget : {SIZE_MAX, workspace_bytes}) {
-        pl = make_plan(p, total_q, kind, max_q_len, multi ? sys_base_items : 0, true, budget);
+        pl = make_plan(p, total_q, kind, max_q_len, multi ? sys_base_items : 0, true, budget, num_prefixes, sys_mean);
         if (multi && !pl.unsupported && pl.bytes > workspace_bytes)
             pl = make_plan(p, total_q, kind, max_q_len, 0, false, budget);
         if (pl.unsupported || pl.bytes <= workspace_bytes) break;
