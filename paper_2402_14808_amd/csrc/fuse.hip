@@ -186,24 +186,36 @@ __global__ __launch_bounds__(kThreads) void cache_append_kernel(const AppendArgs
     if (threadIdx.x < kWave) {
         const int lane = (int)threadIdx.x;
         const int token = token0 + lane;
-        int req = token;
-        if (a.cu_seqlens_q) {                             // requests that end at or before the token
-            req = 0;
+        // The lanes hold the bounds and lengths of 64 requests at a time, so that a token's place is one trip
+        // to its block id away once they are here (searched first and asked for then, the lengths were a
+        // trip of their own).
+        int req = token, pos = 0;
+        if (a.cu_seqlens_q) {
+            bool found = false;
+            req = a.batch - 1;
             for (int base = 0; base < a.batch; base += kWave) {
-                const int end = base + lane < a.batch ? a.cu_seqlens_q[base + lane + 1] : INT_MAX;
+                const int r = base + lane;
+                const bool any = r < a.batch;
+                const int first = any ? a.cu_seqlens_q[r] : 0, end = any ? a.cu_seqlens_q[r + 1] : INT_MAX;
+                const int len = any ? a.context_lens[r] : 0;
+                int owner = kWave;                        // requests of these that end at or before the token
                 for (int t = 0; t < tpw; ++t) {
                     const int ended = __builtin_popcountll(__builtin_amdgcn_ballot_w64(end <= token0 + t));
-                    if (lane == t) req += ended;
+                    if (lane == t) owner = ended;
+                }
+                // (a token that no request owns goes to the last one)
+                const bool last = base + kWave >= a.batch;
+                const int from = min(owner, min(a.batch - base, kWave) - 1);
+                const int f = __shfl(first, from), e = __shfl(end, from), l = __shfl(len, from);
+                if (!found && (owner < kWave || last)) {
+                    found = true;
+                    req = base + from;
+                    pos = l - (e - f) + (token - f);
                 }
             }
-            req = min(req, a.batch - 1);
         }
         if (lane < tpw && token < a.total_q) {
-            int pos = a.context_lens[req] - 1;
-            if (a.cu_seqlens_q) {
-                const int q0 = a.cu_seqlens_q[req], q1 = a.cu_seqlens_q[req + 1];
-                pos += 1 - (q1 - q0) + (token - q0);
-            }
+            if (!a.cu_seqlens_q) pos = a.context_lens[req] - 1;
             int64_t dst = -1;                             // malformed lengths: write nothing
             if (pos >= 0) {
                 const int64_t blk = a.block_tables[(int64_t)req * a.max_blocks_per_seq + (pos >> a.block_size_log2)];
