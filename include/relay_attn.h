@@ -128,6 +128,10 @@ size_t relay_attn_workspace_bytes(const ra_params *p, int32_t total_q);
  * A request with sys_len + context_lens[i] == 0 gets a zero output row and
  * lse = -inf.  workspace must be 256-byte aligned; it should hold
  * relay_attn_workspace_bytes(p, batch) bytes.
+ *   A step is two launches (partial attention, fusion) or, where it is small enough (by sys_len,
+ * max_context_len, num_blocks and the number of query rows: around ten microseconds' worth), one
+ * that writes the output itself and leaves the workspace alone.  The same holds for the other
+ * decode entry points.
  */
 ra_status relay_attn_decode(const ra_params *p,
                             const void *q,
@@ -193,8 +197,8 @@ size_t relay_attn_static_scratch_bytes(void);
 /*
  * Measurement aid, not for serving: relay_attn_decode restricted to some of its launches.
  * phases bit 0 = the partial-attention launch (system + context attention into the workspace),
- * bit 1 = the relay-fusion launch (workspace -> out); 3 is relay_attn_decode.  The benchmark
- * times the dominant kernel alone with it.
+ * bit 1 = the relay-fusion launch (workspace -> out); 3 is relay_attn_decode (which may be a
+ * single launch; 1 and 2 always are the two).  The benchmark times the dominant kernel alone with it.
  */
 ra_status relay_attn_debug_decode_phases(const ra_params *p, int32_t phases,
                                          const void *q,
@@ -212,7 +216,8 @@ ra_status relay_attn_debug_decode_phases(const ra_params *p, int32_t phases,
  * system workgroups first in a decode step, see relay_attn_decode_plan) writes the device's
  * 100 MHz real-time counter to timeline[2w] and timeline[2w+1] (DEVICE memory, 8-byte aligned,
  * room for 2 * timeline_wavefronts values; wavefronts beyond that are not recorded; entries of
- * wavefronts that do not exist stay as they were).  The result of the call is the ordinary one.
+ * wavefronts that do not exist stay as they were).  The result of the call is the ordinary one
+ * (a decode step that is ordinarily a single launch has it behind the recorded one).
  */
 ra_status relay_attn_debug_timeline(const ra_params *p,
                                     const void *q,
@@ -226,7 +231,7 @@ ra_status relay_attn_debug_timeline(const ra_params *p,
                                     void *hip_stream);
 
 /*
- * The work decomposition relay_attn_decode would use for these parameters (host only, no HIP
+ * The work decomposition of relay_attn_decode's two-launch form for these parameters (host only, no HIP
  * call; for tuning and for tests of the decomposition).  The partial-attention launch consists of
  * num_sys_workgroups workgroups that each take one (kv head, sys_rows_per_workgroup stacked query
  * rows, sys_chunk_tokens system positions) item, and num_ctx_wavefronts wavefronts that share the

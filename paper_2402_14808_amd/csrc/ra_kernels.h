@@ -74,6 +74,30 @@ struct TileArgs {                // both partial attentions of a decode step in 
     int timeline_waves;
 };
 
+struct DirectArgs {              // a small decode step in one launch (decode_direct.hip)
+    const uint16_t *q, *k_cache, *v_cache;
+    const uint16_t *k_new, *v_new;                 // the step's own rows, written to the cache by the launch; or null
+    const int32_t *block_tables, *context_lens;
+    void *out;
+    float *lse_out;                                // natural log; may be null
+    int64_t q_stride_token, q_stride_head, o_stride_token, o_stride_head, sys_stride_token, sys_stride_head;
+    int64_t new_stride_token, new_stride_head;
+    int n_tokens, Hq, Hkv, G, max_ctx, block_size_log2, max_blocks_per_seq, out_is_fp32;
+    float scale_log2;
+};
+struct DirectOne {               // its system prompt
+    const uint16_t *k, *v;
+    int len;
+};
+struct DirectMany {              // or several: prefix p owns the tokens below token_end[p], unless
+    int n;                       // req_prefix names each token's
+    const int32_t *req_prefix;
+    int token_end[kMaxPrefixes], len[kMaxPrefixes];
+    const uint16_t *k[kMaxPrefixes], *v[kMaxPrefixes];
+};
+template <bool MANY> struct DirectPrefixes { using type = DirectOne; };
+template <> struct DirectPrefixes<true> { using type = DirectMany; };
+
 struct RowsArgs {                // many query rows per kv head: prompt phase, wide decode batches
     const uint16_t *q, *k_sys, *v_sys, *k_cache, *v_cache;
     const int32_t *block_tables, *context_lens;
@@ -136,6 +160,8 @@ struct FuseArgs {                // relay fusion (Alg. 1; Eq. 11 generalised to 
 hipError_t launch_ctx_decode(const CtxArgs &a, int head_dim, int group, hipStream_t stream);
 hipError_t launch_relay_rows(const RowsArgs &a, int head_dim, hipStream_t stream);
 hipError_t launch_relay_tiles(const TileArgs &a, int head_dim, hipStream_t stream);
+hipError_t launch_decode_direct(const DirectArgs &a, const DirectOne *one, const DirectMany *many, int head_dim,
+                                hipStream_t stream);
 hipError_t launch_cache_append(const AppendArgs &a, hipStream_t stream);
 hipError_t launch_system_fill(const SysFillArgs &a, hipStream_t stream);
 

@@ -487,6 +487,30 @@ bool light_if_spare(int64_t sys_wgs, int64_t ctx_wgs) {
     return cus == kReferenceCus && sys_wgs > 0 && sys_wgs <= cus && sys_wgs + ctx_wgs > 2 * cus;
 }
 
+// A decode step small enough is one launch (decode_direct.hip): where the estimate of that form is below 14 us and
+// below the two-launch form's.  Both forms of 345 drawn steps (1 .. 256 requests, 4 .. 52 query heads, prompts of
+// 100 .. 16000, contexts of 4 .. 16000) were timed: 98 took this form, 0.68 - 0.97 of the time (one request of 32/8
+// heads, s = 512, 10.5 -> 7.2 us; 16 of 16 heads of 64, s = 1000, contexts up to 255, 11.3 -> 9.4), the worst of them
+// 1.08; with any limit above 16 us calls of many long contexts turn up to 1.9 times slower, since a
+// workgroup has all of a request's context to itself.  So the longest context is taken to be what the bound
+// and the cache allow, not what they make likely.
+bool direct_form(const ra_params *p, int32_t total_q, int max_ctx, double sys_mean) {
+    if (p->sys_chunk_tokens != 0 || p->ctx_part_tokens != 0 || total_q > 65535) return false;
+    double held = (double)p->num_blocks * p->block_size;
+    if (held < total_q) held = (double)total_q * max_ctx;            // (was not filled in)
+    const double longest = held < max_ctx ? held : max_ctx, mean = held / total_q < max_ctx ? held / total_q : max_ctx;
+    const double workgroups = (double)total_q * p->num_q_heads, row_bytes = 4.0 * p->head_dim;
+    const double rate = p->head_dim == 128 ? 300 : 460;              // rows of a workgroup per us
+    const double one = (p->sys_len + longest) / rate, even = (sys_mean + mean) / rate * workgroups / 256,
+                 moved = workgroups * (sys_mean + mean) * row_bytes / 16.8e6;
+    const double most = one > even ? (one > moved ? one : moved) : (even > moved ? even : moved);
+    const double direct_us = 6.5 + most + 1.3 * (ceil(workgroups / 256) - 1);
+    const double tiles = ceil(total_q * (double)(p->num_q_heads / p->num_kv_heads) / 32);
+    const double mb = (tiles * sys_mean + total_q * mean) * p->num_kv_heads * row_bytes / 1e6;
+    const double tile_us = 9.4 + mb / 8.9 + 0.34 * log2(1 + mb) + workgroups * 0.56e-3;
+    return direct_us < 14 && direct_us < tile_us;
+}
+
 // Where the partial-attention launch records the begin and end of its wavefronts (measurement aid).
 struct Timeline {
     unsigned long long *entries = nullptr;   // device, 2 per wavefront
@@ -585,6 +609,57 @@ ra_status run(const ra_params *p, const void *q, const int32_t *cu_seqlens_q, in
 
     const bool prefill = cu_seqlens_q != nullptr;
     const int head_fastest = p->sys_stride_head < p->sys_stride_token ? 1 : 0;
+
+    // A small decode step in one launch.  (A timeline is one of the two-launch form: it is taken of the partial
+    // attention, and the result is this form's all the same.)
+    const bool direct_step = !naive && !prefill && mask == 3 && direct_form(p, total_q, pl.max_ctx, sys_mean);
+    auto launch_direct_step = [&]() -> ra_status {
+        ra::DirectArgs d{};
+        d.q = static_cast<const uint16_t *>(q);
+        d.k_cache = static_cast<const uint16_t *>(k_cache);
+        d.v_cache = static_cast<const uint16_t *>(v_cache);
+        if (append) {
+            d.k_new = static_cast<const uint16_t *>(append->k);
+            d.v_new = static_cast<const uint16_t *>(append->v);
+            d.new_stride_token = append->stride_token;
+            d.new_stride_head = append->stride_head;
+        }
+        d.block_tables = block_tables;
+        d.context_lens = context_lens;
+        d.out = out;
+        d.lse_out = lse_out;
+        d.q_stride_token = p->q_stride_token;
+        d.q_stride_head = p->q_stride_head;
+        d.o_stride_token = p->o_stride_token;
+        d.o_stride_head = p->o_stride_head;
+        d.sys_stride_token = p->sys_stride_token;
+        d.sys_stride_head = p->sys_stride_head;
+        d.n_tokens = total_q;
+        d.Hq = p->num_q_heads;
+        d.Hkv = p->num_kv_heads;
+        d.G = pl.group;
+        d.max_ctx = pl.max_ctx;
+        d.block_size_log2 = pl.block_size_log2;
+        d.max_blocks_per_seq = p->max_blocks_per_seq;
+        d.out_is_fp32 = p->out_is_fp32;
+        d.scale_log2 = scale_log2;
+        ra::DirectOne one{static_cast<const uint16_t *>(prefixes[0].k_sys),
+                          static_cast<const uint16_t *>(prefixes[0].v_sys), prefixes[0].sys_len};
+        ra::DirectMany many{};
+        if (num_prefixes > 1) {
+            many.n = num_prefixes;
+            many.req_prefix = req_prefix;
+            for (int i = 0; i < num_prefixes; ++i) {
+                many.token_end[i] = tok0[i] + ntok[i];
+                many.len[i] = prefixes[i].sys_len;
+                many.k[i] = static_cast<const uint16_t *>(prefixes[i].k_sys);
+                many.v[i] = static_cast<const uint16_t *>(prefixes[i].v_sys);
+            }
+        }
+        return ra::launch_decode_direct(d, num_prefixes > 1 ? nullptr : &one, num_prefixes > 1 ? &many : nullptr,
+                                        p->head_dim, stream) == hipSuccess ? RA_OK : RA_ERR_HIP;
+    };
+    if (direct_step && !timeline) return launch_direct_step();
 
     // Prompt phase in ONE launch: a work item carries its 128 rows through the system prompt and then
     // through the contexts of the requests they belong to, and writes the output itself; no
@@ -745,6 +820,7 @@ ra_status run(const ra_params *p, const void *q, const int32_t *cu_seqlens_q, in
         t.scale_log2 = scale_log2;
         if (timeline) t.timeline = timeline->entries, t.timeline_waves = timeline->waves;
         if (ra::launch_relay_tiles(t, p->head_dim, stream) != hipSuccess) return RA_ERR_HIP;
+        if (direct_step) return launch_direct_step();
     }
     // The per-request comparison path.
     if ((mask & 1) && naive) {
