@@ -367,11 +367,8 @@ __device__ __forceinline__ void attend(const TileArgs &a, const Item &it, const 
         sm_m[wave][col] = m_run;
         sm_l[wave][col] = l_run;
     }
-    __syncthreads();   // also: every wavefront is done with its K/V slice
-    float M_all = sm_m[0][col];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) M_all = fmaxf(M_all, sm_m[w][col]);
-    const float f_mine = fast_exp2(m_run - finite_or_zero(M_all));
+    // (a wavefront's slice is its own: it puts its sums there as they are as soon as it is done, and the
+    // readers weight them; scaled by the writers, the merge took a second barrier)
     float *osh = reinterpret_cast<float *>(my) + col * D;      // merge buffer row of this lane
     constexpr int OCH = D / 4;                    // 16-byte chunks per fp32 output row
     if (col < ncols) {
@@ -379,8 +376,7 @@ __device__ __forceinline__ void attend(const TileArgs &a, const Item &it, const 
         for (int db = 0; db < T::DBLK; ++db)
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
-                f32x4 v = {acc_o[db][4 * r4] * f_mine, acc_o[db][4 * r4 + 1] * f_mine,
-                           acc_o[db][4 * r4 + 2] * f_mine, acc_o[db][4 * r4 + 3] * f_mine};
+                const f32x4 v = {acc_o[db][4 * r4], acc_o[db][4 * r4 + 1], acc_o[db][4 * r4 + 2], acc_o[db][4 * r4 + 3]};
                 const int chunk = (db * 8 + 2 * r4 + hf) ^ (col & (OCH - 1));
                 *reinterpret_cast<f32x4 *>(osh + chunk * 4) = v;
             }
@@ -394,9 +390,12 @@ __device__ __forceinline__ void attend(const TileArgs &a, const Item &it, const 
 #pragma unroll
         for (int w = 1; w < kWaves; ++w) Mr = fmaxf(Mr, sm_m[w][row]);
         const float m_use = finite_or_zero(Mr);
-        float L = 0.f;
+        float L = 0.f, f[kWaves];
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) L = fmaf(sm_l[w][row], fast_exp2(sm_m[w][row] - m_use), L);
+        for (int w = 0; w < kWaves; ++w) {
+            f[w] = fast_exp2(sm_m[w][row] - m_use);
+            L = fmaf(sm_l[w][row], f[w], L);
+        }
         const float inv = L > 0.f ? 1.f / L : 0.f;
         int token, hq;
         column_row(row, token, hq);
@@ -409,7 +408,7 @@ __device__ __forceinline__ void attend(const TileArgs &a, const Item &it, const 
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) {
                 const float *src = reinterpret_cast<const float *>(smem + w * T::SLICE) + row * D;
-                sum += *reinterpret_cast<const f32x4 *>(src + chunk * 4);
+                sum += *reinterpret_cast<const f32x4 *>(src + chunk * 4) * f[w];
             }
             *reinterpret_cast<f32x4 *>(dst + e) = sum * inv;
         }
