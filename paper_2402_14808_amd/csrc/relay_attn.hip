@@ -249,10 +249,11 @@ constexpr int kRowsSysMinTiles = 8;
 // Work decomposition; a pure function of (params, total_q) so that the workspace size the
 // caller asked for and the one the launch uses always agree.  A `budget` below that size asks for
 // the fewest partials: the cut that a caller's workspace of fixed size, made for another batch, may
-// still hold (the size does not only rise with the batch).
+// still hold (the size does not only rise with the batch).  `by_bound` plans a decode step for contexts
+// as long as the bound allows, whatever the cache holds.
 Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q_len,
                int64_t sys_base_items = 0, bool allow_rows_sys = true, size_t budget = SIZE_MAX, int num_groups = 1,
-               double sys_mean = -1) {
+               double sys_mean = -1, bool by_bound = false) {
     Plan pl{};
     const bool tight = budget != SIZE_MAX;
     const bool prefill = kind == kPrefill;
@@ -298,7 +299,22 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
                                                       : (int64_t)p->num_kv_heads * pl.n_mtiles;
         const int64_t t_max = pl.max_ctx > 0 ? ceil_div(pl.max_ctx, 32) : 0;   // tiles of one context
         const int64_t ctx_tiles = (int64_t)total_q * p->num_kv_heads * t_max;
-        const int64_t all_tiles = base_items * sys_tiles + ctx_tiles;
+        // What the launch is planned for: the contexts at the bound, or as many of their tiles as the cache can
+        // hold where those are fewer (a num_blocks that does not even hold a token each was not filled in): a bound
+        // twenty times the contexts had 7100 tiles planned for where 180 were there (18 requests of 32 heads, 3 .. 21
+        // tokens behind s = 1008, 20.7 -> 14.8 us; contexts of 859 .. 1706 under a wider bound 23.3 -> 20.9).
+        // Slots and the fewest workgroups stay those of the bound, so any lengths up to it are served.
+        // Batches wide enough for many-rows items take it for short contexts only: with longer ones the even
+        // launch that the bound leads to was faster (40 requests of 28/4 heads, contexts of 37 .. 310, 19.7 against 22.3
+        // us; 153 of them, 425 .. 601, 47.5 against 52.7).
+        int64_t ctx_like = ctx_tiles;
+        if (!by_bound) {
+            const int64_t held = (int64_t)p->num_blocks * p->block_size;
+            const int64_t tiles = p->num_kv_heads * (held / 32 + (total_q + 1) / 2);
+            const bool many_rows = pl.n_mtiles >= 4 && tiles >= 4 * (int64_t)total_q * p->num_kv_heads;
+            if (held >= total_q && tiles < ctx_like && !many_rows) ctx_like = tiles;
+        }
+        const int64_t all_tiles = base_items * sys_tiles + ctx_like;
         if (ctx_tiles > INT32_MAX) {
             pl.unsupported = true;
             return pl;
@@ -324,9 +340,9 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
         // batch 128 of the Llama-30B shape at s = 8192 157 -> 128 us, batch 192 at 4096 163 -> 144 us.
         {
             const int64_t sys_all = base_items * sys_tiles;
-            const bool wide = pl.n_mtiles >= kRowsSysMinTiles && 2 * sys_all >= ctx_tiles;
+            const bool wide = pl.n_mtiles >= kRowsSysMinTiles && 2 * sys_all >= ctx_like;
             const bool full_block = pl.n_mtiles >= 4 && sys_all >= 64 * (kWorkgroupSlots / 2) &&
-                                    sys_all >= ctx_tiles;
+                                    sys_all >= ctx_like;
             pl.rows_sys = allow_rows_sys && sys_base_items == 0 && p->sys_len > 0 && (wide || full_block);
         }
         if (pl.rows_sys) {
@@ -373,10 +389,10 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
                 const int64_t tiles = chunk / 32, up = tiles / 4 * 4 + 4;
                 if (t_star16 <= 40 && tiles > 4 && tiles % 4 != 0) {
                     const int64_t like16 = up * 4 > t_star16 ? up * 4 : t_star16;
-                    const int64_t units = kWorkgroupSlots / 2, ctx_like = (ctx_tiles * 16 + 4 * like16 - 1) / (4 * like16);
+                    const int64_t units = kWorkgroupSlots / 2, ctx_like_wgs = (ctx_like * 16 + 4 * like16 - 1) / (4 * like16);
                     auto wgs_at = [&](int64_t t) { return base_items * ((sys_tiles + t - 1) / t); };
-                    const int64_t total = wgs_at(tiles) + ctx_like;
-                    if (total > units && total <= units * 5 / 4 && wgs_at(up) + ctx_like <= units) chunk = (int)up * 32;
+                    const int64_t total = wgs_at(tiles) + ctx_like_wgs;
+                    if (total > units && total <= units * 5 / 4 && wgs_at(up) + ctx_like_wgs <= units) chunk = (int)up * 32;
                 }
             }
             pl.sys_chunk = chunk;
@@ -405,7 +421,25 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
             } else {
                 const int64_t least = (ctx_tiles + 4 * t_cap - 1) / (4 * t_cap);
                 const int64_t t_like16 = t_sys * 16 > t_star16 ? t_sys * 16 : t_star16;
-                wgs = (ctx_tiles * 16 + 4 * t_like16 - 1) / (4 * t_like16);
+                wgs = (ctx_like * 16 + 4 * t_like16 - 1) / (4 * t_like16);
+                // Short contexts: a wavefront of few tiles has as many contexts to begin, each with a chain of
+                // trips of its own (length, block ids, rows: about 3 us next to 0.9 for a tile), so it takes
+                // fewer of them than the turns of a system workgroup leave room for (a step of a many-rows item is
+                // about half a turn), as long as the machine has places.  245 requests of 28/4 heads, contexts of
+                // 21 .. 30, s = 437: 35.5 -> 21.2 us; 7 of 32 heads, 5 .. 17, s = 5429: 32.0 -> 24.2; 145 of 40 heads,
+                // 30 .. 40, s = 162: 71 -> 47; longer contexts come out as before.
+                const double t_item = (double)ctx_like / ((double)total_q * p->num_kv_heads);
+                if (!by_bound) {
+                    const double turns = (pl.rows_sys ? 0.5 * t_sys : sys_wgs > 0 ? t_sys : t_star) + 2.5;
+                    double per_wave = turns / (0.9 + 3.0 / (t_item > 1 ? t_item : 1));
+                    if (per_wave < 1) per_wave = 1;
+                    // (and no fewer workgroups than the bound would have, where there are places for them)
+                    int64_t more = (int64_t)ceil(ctx_like / (4 * per_wave));
+                    const int64_t bound = (ctx_tiles * 16 + 4 * t_like16 - 1) / (4 * t_like16);
+                    if (bound > more) more = bound;
+                    if (more > kWorkgroupSlots - sys_wgs) more = kWorkgroupSlots - sys_wgs;
+                    if (more > wgs) wgs = more;
+                }
                 // when the launch is about one machine-full of equally long wavefronts, make it
                 // exactly one
                 if (all_tiles > (int64_t)kWaveSlots * kMinWaveTiles && sys_wgs <= kWorkgroupSlots * 7 / 8 &&
@@ -423,6 +457,25 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
                 }
                 if (wgs < least) wgs = least;
                 if (wgs < 1) wgs = 1;
+                // The rule for even units gives what a unit without a system workgroup has left over to its context
+                // wavefronts.  With short contexts the few such units can be what the launch waits for (50 requests
+                // of 40 heads, contexts of 9 .. 56 behind s = 1792, 240 system workgroups: system parts done at 17 us,
+                // the 32 other workgroups at 27).  An estimate of both sides in us (a tile's share of the memory a
+                // unit can draw; a wavefront's own 1.2 a tile and 5 a context begun) takes equal spans then:
+                // 94 requests of 40 heads, 10 .. 29, s = 11916 115 -> 84 us, 93 of them, 48 .. 61, s = 1604 45.8 -> 37.8,
+                // 204 of 32/8, 12 .. 24, three prompts 34.7 -> 25.6; slower where it errs (84 of 40 heads,
+                // 13 .. 42, prompts of 100 .. 153: 24.2 -> 26.6).  With contexts of 30 tiles it did: 71 -> 77.
+                if (pl.paired && t_item < 4 && !by_bound) {
+                    const double step = pl.rows_sys ? (double)pl.sys_chunk / 32 : (double)ceil_div(pl.sys_chunk, 32);
+                    const double n = (double)ctx_like, even = n / (double)wgs;
+                    const double draw = p->head_dim == 128 ? 0.59 : 0.3, each = 1.2 + 5.0 / (t_item > 1 ? t_item : 1);
+                    auto longer = [](double a, double b) { return a > b ? a : b; };
+                    const double light = longer(0, ((double)base_items * sys_tiles + n) / (kWorkgroupSlots / 2) - step);
+                    const double heavy = wgs > sys_wgs ? (n - light * (double)sys_wgs) / (double)(wgs - sys_wgs) : 0;
+                    const double by_unit = longer(longer(draw * (step + light), draw * 2 * heavy), each * longer(heavy, light) / 4);
+                    const double equal = longer(longer(draw * (step + even), draw * 2 * even), each * even / 4);
+                    if (equal < by_unit) pl.paired = false;
+                }
                 // t_est: tiles per wavefront if every context had the maximum length.  Real
                 // lengths are shorter and the spans shrink with them, down to the floor below; a
                 // floor near t_est would leave most context wavefronts without work (a batch
@@ -434,23 +487,34 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
                 // static scratch unless even a floor of t_est itself takes more.
                 // (12 requests, 8 kv heads, contexts 1500 .. 15000: 95.9 -> 73.5 us with
                 // spans of 12 tiles on every wavefront instead of 24 on half of them)
-                const int64_t t_est = (ctx_tiles + 4 * wgs - 1) / (4 * wgs);
-                int64_t slots = (t_max + t_est - 1) / t_est + 1;
+                // (short contexts, up to 8 tiles, go by the tiles that are there: spans of one tile behind a loose
+                // bound, 15.2 -> 10.9 us at 12 requests of 8 heads, 8 .. 76 tokens; for longer ones the partials
+                // of so many spans cost more than they give, 17.0 -> 20.9 at 6 of 28/4 heads, 1240 .. 5082)
+                auto parts = [&](int64_t t) { return (t_max + t - 1) / t + 1; };
+                const int64_t t_bound = (ctx_tiles + 4 * wgs - 1) / (4 * wgs);
+                const int64_t t_est = t_item < 8 ? (ctx_like + 4 * wgs - 1) / (4 * wgs) : t_bound;
+                int64_t slots = parts(t_bound);
                 int64_t t_low = (t_est + 7) / 8;
                 if (t_low < kMinWaveTiles) t_low = kMinWaveTiles < t_est ? kMinWaveTiles : t_est;
-                int64_t wide = (t_max + t_low - 1) / t_low + 1;
+                int64_t wide = parts(t_low);
                 const size_t most = budget < kStaticScratchBytes ? budget : kStaticScratchBytes;
                 const int64_t room = (int64_t)((most > 512 ? most - 512 : 0) / ((size_t)pl.rows * (d * 4 + 4))) -
                                      pl.n_sys_chunks;
-                pl.n_ctx_likely = (int)slots;
                 if (wide > room) wide = room;
                 if (wide > slots) slots = wide;
                 pl.n_ctx_parts = (int)slots;
+                pl.n_ctx_likely = (int)(parts(t_est) < slots ? parts(t_est) : slots);
                 pl.ctx_t_floor = (int)((t_max + slots - 2) / (slots - 1));
             }
             pl.ctx_wgs = (int)wgs;
         }
         finish();
+        // A plan that outgrows the workspace or the static scratch takes no more than the bound's.
+        if (!by_bound && pl.bytes > (budget < kStaticScratchBytes ? budget : kStaticScratchBytes)) {
+            const Plan bound = make_plan(p, total_q, kind, max_q_len, sys_base_items, allow_rows_sys, budget, num_groups,
+                                         sys_mean, true);
+            if (!bound.unsupported && bound.bytes < pl.bytes) return bound;
+        }
         return pl;
     }
 
@@ -567,7 +631,10 @@ ra_status run(const ra_params *p, const void *q, const int32_t *cu_seqlens_q, in
     }
     const PlanKind kind = cu_seqlens_q ? kPrefill : naive ? kNaiveDecode : kRelayDecode;
     // A caller sizes the workspace without knowing the grouping; should the grouping-aware plan
-    // need more than that, the grouping-blind one (which is what the size was computed from) is used.
+    // need more than that, a decode step takes the fewest slots with it (the blind plan does not count the
+    // prefixes' workgroups and launched more than the machine holds: 19 requests of 40 heads, two prompts
+    // of 1989 and 2830, 60.5 against 39.3 us), and otherwise the grouping-blind one (which is what the size
+    // was computed from) is used.
     // Where the workspace is smaller than either, the cut with the fewest partials may still fit it.
     const bool multi = num_prefixes > 1;
     double sys_mean = 0;
@@ -575,6 +642,8 @@ ra_status run(const ra_params *p, const void *q, const int32_t *cu_seqlens_q, in
     Plan pl{};
     for (size_t budget : {SIZE_MAX, workspace_bytes}) {
         pl = make_plan(p, total_q, kind, max_q_len, multi ? sys_base_items : 0, true, budget, num_prefixes, sys_mean);
+        if (multi && kind == kRelayDecode && !pl.unsupported && pl.bytes > workspace_bytes)
+            pl = make_plan(p, total_q, kind, max_q_len, sys_base_items, true, workspace_bytes);
         if (multi && !pl.unsupported && pl.bytes > workspace_bytes)
             pl = make_plan(p, total_q, kind, max_q_len, 0, false, budget);
         if (pl.unsupported || pl.bytes <= workspace_bytes) break;
@@ -896,6 +965,11 @@ size_t relay_attn_workspace_bytes(const ra_params *p, int32_t total_q) {
     // (a call with several prefixes may fall back to the decode plan without many-rows items)
     const Plan blind = make_plan(p, total_q, kRelayDecode, 1, 0, false);
     if (!blind.unsupported && blind.bytes > most) most = blind.bytes;
+    // (and a workspace serves calls over a cache of another size)
+    for (const bool rows_sys : {true, false}) {
+        const Plan bound = make_plan(p, total_q, kRelayDecode, 1, 0, rows_sys, SIZE_MAX, 1, -1, true);
+        if (!bound.unsupported && bound.bytes > most) most = bound.bytes;
+    }
     return most;
 }
 
