@@ -4,7 +4,8 @@
 //
 // Bound: the chain of dependent trips, not bytes (one request of 32/8 heads, s = 512, 90 positions of
 // context moves 2.5 MB).  The two-launch form needs arguments -> lengths -> block ids -> keys/values ->
-// partials, then a second launch that reads the partials: 8 + 2.5 us for that call.  Here the block ids are
+// partials, then a second launch that reads the partials: 8 + 2.5 us for that call, 7.0 in this form (16 requests of
+// 16 heads of 64, s = 1000, contexts of 16 .. 255: 11.2 and 8.3).  Here the block ids are
 // asked for together with the length, all keys of such a call are in flight at once (16 wavefronts of up to
 // 32 rows each), and the wavefronts meet in LDS.  The query heads of a kv head re-read its rows, from
 // L2 where the kv head is the fastest grid index; what that and re-reading the system prompt per request costs

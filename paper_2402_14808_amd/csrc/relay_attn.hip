@@ -554,7 +554,7 @@ bool light_if_spare(int64_t sys_wgs, int64_t ctx_wgs) {
 // A decode step small enough is one launch (decode_direct.hip): where the estimate of that form is below 14 us and
 // below the two-launch form's.  Both forms of 345 drawn steps (1 .. 256 requests, 4 .. 52 query heads, prompts of
 // 100 .. 16000, contexts of 4 .. 16000) were timed: 98 took this form, 0.68 - 0.97 of the time (one request of 32/8
-// heads, s = 512, 10.5 -> 7.2 us; 16 of 16 heads of 64, s = 1000, contexts up to 255, 11.3 -> 9.4), the worst of them
+// heads, s = 512, 10.5 -> 7.2 us; 16 of 16 heads of 64, s = 1000, contexts up to 255, 11.3 -> 8.3), the worst of them
 // 1.08; with any limit above 16 us calls of many long contexts turn up to 1.9 times slower, since a
 // workgroup has all of a request's context to itself.  So the longest context is taken to be what the bound
 // and the cache allow, not what they make likely.
@@ -789,10 +789,20 @@ ra_status run(const ra_params *p, const void *q, const int32_t *cu_seqlens_q, in
             if (r.n_ctx_parts < 1 || r.ctx_part < 1) r.n_ctx_parts = 0, r.ctx_part = 1;   // no context at all
         }
         if (num_prefixes > 1) {                    // system items prefix by prefix
-            int by_len[ra::kMaxPrefixes];          // the longest first: their items are what the launch would wait for
+            // Whole items start with the longest prompt's, which the launch would wait for, where there are more than the
+            // machine holds at once (800 items of 1304 .. 1616 positions 0.93 of the time, 764 of 870 .. 2933 0.94) or
+            // prompts are long (476 items of 2712 .. 10379 0.92, 296 of 3436 .. 8295 0.87).  Short ones that all start
+            // together only change which of them share a unit: between 0.92 and 1.04 of 8 such launches, three
+            // prompts of 300 .. 2000 68.0 us as given and 69.4 by length; the line lies between 2600 and 8300.
+            int by_len[ra::kMaxPrefixes], whole_items = 0, longest = 0;
+            for (int i = 0; whole && i < num_prefixes; ++i) {
+                whole_items += p->num_kv_heads * ceil_div(ntok[i] * pl.group, 128);
+                if (prefixes[i].sys_len > longest) longest = prefixes[i].sys_len;
+            }
+            const bool sorted = whole_items > 2 * device_compute_units() || longest >= 4096;
             for (int i = 0; i < num_prefixes; ++i) {
                 int at = i;
-                for (; whole && at > 0 && prefixes[by_len[at - 1]].sys_len < prefixes[i].sys_len; --at) by_len[at] = by_len[at - 1];
+                for (; sorted && at > 0 && prefixes[by_len[at - 1]].sys_len < prefixes[i].sys_len; --at) by_len[at] = by_len[at - 1];
                 by_len[at] = i;
             }
             int items = 0;

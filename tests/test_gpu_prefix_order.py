@@ -1,4 +1,4 @@
-"""The one-launch prompt phase with several prefixes starts its items with the longest prompt's: any order of the
+"""The one-launch prompt phase with several prefixes starts its items with the longest prompt's where they are many: any order of the
 lengths, equal and empty ones among them, gives every group its own prompt."""
 import numpy as np
 import pytest
@@ -11,7 +11,7 @@ TOL, LSE_TOL = 2e-3, 1e-3          # as in the other parity tests: fp32 output, 
 
 
 @pytest.mark.parametrize("lens", [(40, 90, 200, 200), (200, 0, 90, 40), (90, 200, 0, 90), (1, 64, 65, 129)])
-@pytest.mark.parametrize("d,Hq,Hkv", [(128, 4, 1), (64, 3, 3)])
+@pytest.mark.parametrize("d,Hq,Hkv", [(128, 4, 1), (64, 3, 3), (64, 132, 132)])     # the last: more than 512 items
 def test_any_order_of_prompt_lengths(lens, d, Hq, Hkv):
     cfg = W.AttnConfig(name="po", batch=6, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, sys_len=max(lens), ctx_lo=0,
                        ctx_hi=40, block_size=16, q_lo=33, q_hi=70)
