@@ -349,8 +349,8 @@ ra_status relay_attn_decode_grouped(const ra_params *p,
  * The workspace is required as for the decode step (relay_attn_workspace_bytes(p, total_q)).  A
  * call runs as a single launch that does not touch it (the relay fusion of Alg. 1 happens in the
  * accumulators) if it brings at least 32 new tokens per request on average (4 when the system
- * prompt has at most 1024 positions), its system prompt is one chunk of work, contexts are not what
- * the launch would wait for (by max_context_len and by what num_blocks can hold) and
+ * prompt has at most 1024 positions), an estimate of both forms (by the new tokens, the prompt,
+ * max_context_len and what num_blocks can hold) has that one faster or the walk is short, and
  * p->sys_chunk_tokens / ctx_part_tokens are not set by hand; other calls write
  * partials there and fuse them in a second launch.  The results agree within the tolerance, not
  * bit for bit, between the two forms.
