@@ -4,10 +4,12 @@
 //
 // Bound: the chain of dependent trips, not bytes (one request of 32/8 heads, s = 512, 90 positions of
 // context moves 2.5 MB).  The two-launch form needs arguments -> lengths -> block ids -> keys/values ->
-// partials, then a second launch that reads the partials: 8 + 2.5 us for that call, 7.0 in this form (16 requests of
-// 16 heads of 64, s = 1000, contexts of 16 .. 255: 11.2 and 8.3).  Here the block ids are
-// asked for together with the length, all keys of such a call are in flight at once (16 wavefronts of up to
-// 32 rows each), and the wavefronts meet in LDS.  The query heads of a kv head re-read its rows, from
+// partials, then a second launch that reads the partials: 8 + 2.5 us for that call, 6.9 in this form (16 requests of
+// 16 heads of 64, s = 1000, contexts of 16 .. 255: 10.8 and 7.8).  Here the trips are arguments -> length -> block
+// ids -> keys/values (system rows do not wait for the two in the middle), and the wavefronts meet in LDS.  16
+// wavefronts hold up to 16 (head_dim 128) or 32 rows each and ask for as many again while they work: 512 rows of
+// a call at head_dim 128, 1024 at 64.  (Block ids come back behind the rows that were asked for before them, so a
+// second batch of context rows starts when the first has landed.)  The query heads of a kv head re-read its rows, from
 // L2 where the kv head is the fastest grid index; what that and re-reading the system prompt per request costs
 // is why the form is for small calls only (see direct_form in relay_attn.hip for the line).
 // Vector arithmetic: with one query row there is no matrix product, and the row's 16 (head_dim 128) or 8
@@ -19,6 +21,12 @@ namespace ra {
 
 constexpr int kDirectWaves = 16;
 constexpr int kDirectThreads = kDirectWaves * kWave;
+
+// Block-table slot to read for row `row` of [s system rows ; a context that is not empty]: the row's own, and the
+// first one for a system row, so that no slot behind the ones in use is ever read.
+__host__ __device__ constexpr int used_slot(int row, int s, int block_size_log2) {
+    return row < s ? 0 : (row - s) >> block_size_log2;
+}
 
 template <int D, bool MULTI, bool APPEND>
 __global__ __launch_bounds__(kDirectThreads, 4) void decode_direct_kernel(
@@ -71,27 +79,23 @@ __global__ __launch_bounds__(kDirectThreads, 4) void decode_direct_kernel(
             }
             return;
         }
-        int blk[U];
+        // Every block id of the batch before its first row: an id asked for between the rows makes each row wait for
+        // the ones before it (12 requests of 32/8 heads, s = 115, contexts of 144 .. 218: 10.5 us so, 9.4 as here).
+        int row[U], blk[U] = {};
 #pragma unroll
-        for (int u = 0; u < U; ++u) {             // (in the table whatever the length is: not behind it yet)
-            const int pos = max(base + u * TPI + grp - s, 0) >> bsl;
-            blk[u] = a.max_ctx > 0 ? bt[min(pos, a.max_blocks_per_seq - 1)] : 0;
+        for (int u = 0; u < U; ++u) row[u] = min(base + u * TPI + grp, total - 1);
+        if (c > 0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) blk[u] = bt[used_slot(row[u], s, bsl)];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int row = min(base + u * TPI + grp, total - 1), pos = row - s;
-            const uint16_t *kp = k_sys, *vp = v_sys;
-            int64_t off = (int64_t)row * a.sys_stride_token;
-            if (pos >= 0) {
-                // (a row behind the end takes the last row's place in a block of its own only if that is its block)
-                const int64_t id = row == base + u * TPI + grp ? blk[u] : bt[pos >> bsl];
-                kp = a.k_cache, vp = a.v_cache;
-                off = (((id * a.Hkv + g) << bsl) + (pos & bmask)) * (int64_t)D;
-                if (APPEND && pos == c - 1) {     // the step's own row: not in the cache yet
-                    kp = a.k_new, vp = a.v_new;
-                    off = (int64_t)token * a.new_stride_token + (int64_t)g * a.new_stride_head;
-                }
-            }
+            const int pos = row[u] - s;
+            const bool sys = pos < 0, fresh = APPEND && pos >= 0 && pos == c - 1;   // fresh: not in the cache yet
+            int64_t off = sys ? (int64_t)row[u] * a.sys_stride_token
+                              : ((((int64_t)blk[u] * a.Hkv + g) << bsl) + (pos & bmask)) * (int64_t)D;
+            if (fresh) off = (int64_t)token * a.new_stride_token + (int64_t)g * a.new_stride_head;
+            const uint16_t *kp = sys ? k_sys : fresh ? a.k_new : a.k_cache, *vp = sys ? v_sys : fresh ? a.v_new : a.v_cache;
             k[u] = *reinterpret_cast<const u32x4 *>(kp + off + sub * 8);
             v[u] = *reinterpret_cast<const u32x4 *>(vp + off + sub * 8);
         }
