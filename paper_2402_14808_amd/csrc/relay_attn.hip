@@ -559,25 +559,35 @@ bool light_if_spare(int64_t sys_wgs, int64_t ctx_wgs) {
 }
 
 // A decode step small enough is one launch (decode_direct.hip): where the estimate of that form is below 14 us and
-// below the two-launch form's.  Both forms of 345 drawn steps (1 .. 256 requests, 4 .. 52 query heads, prompts of
-// 100 .. 16000, contexts of 4 .. 16000) were timed: 98 took this form, 0.68 - 0.97 of the time (one request of 32/8
-// heads, s = 512, 10.5 -> 7.2 us; 16 of 16 heads of 64, s = 1000, contexts up to 255, 11.3 -> 8.3), the worst of them
-// 1.08; with any limit above 16 us calls of many long contexts turn up to 1.9 times slower, since a
-// workgroup has all of a request's context to itself.  So the longest context is taken to be what the bound
-// and the cache allow, not what they make likely.
+// below the two-launch form's, and no request takes too many rounds of its workgroup.  Both forms of 306 drawn
+// steps (1 .. 64 requests and some to 256, 4 .. 52 query heads, prompts of 30 .. 3500 and some to 16000, contexts of 8 ..
+// 3000 and some to 10000) were timed: 177 take this form, two of them at 1.04 and 1.05 of the two-launch time and
+// the others faster (one request of 32/8 heads, s = 512, 10.3 -> 6.9 us; 16 of 16 heads of 64, s = 1000, contexts up to
+// 255, 10.8 -> 7.8), and over all the choice is 1.7 % over the faster form.  The longest context is taken to be what
+// the bound and the cache allow, not what they make likely.
+//   Rounds: 16 wavefronts take 256 rows (head_dim 128; 512 at 64) of a request a round, and past the second a
+// round costs 1.4 us (1 .. 2 rounds 5.3 us, 3 7.2, 4 8.8, 5 11, 6 12.3, 8 15.5).  So up to four are taken, up to six where
+// three or fewer are context (those cost more, and the two-launch form spreads a context over the machine), and
+// five where the two launches wait for memory.  Without these limits ten of the steps were more than 5 % slower in this
+// form (10 requests of 8 heads, contexts of 287 .. 1540, 14.8 us in two launches and 19.3 in one).
+//   Workgroups: 256 fit the machine.  As many again cost 1.3 us, and 1.8 without query groups, where two launches
+// have no less to work on at once (50 requests of 16 heads of 64, s = 42, 7.9 us in two and 10.6 in one).
 bool direct_form(const ra_params *p, int32_t total_q, int max_ctx, double sys_mean) {
     if (p->sys_chunk_tokens != 0 || p->ctx_part_tokens != 0 || total_q > 65535) return false;
     double held = (double)p->num_blocks * p->block_size;
     if (held < total_q) held = (double)total_q * max_ctx;            // (was not filled in)
     const double longest = held < max_ctx ? held : max_ctx, mean = held / total_q < max_ctx ? held / total_q : max_ctx;
     const double workgroups = (double)total_q * p->num_q_heads, row_bytes = 4.0 * p->head_dim;
+    const int group = p->num_q_heads / p->num_kv_heads;
+    const double tiles = ceil(total_q * (double)group / 32);
+    const double mb = (tiles * sys_mean + total_q * mean) * p->num_kv_heads * row_bytes / 1e6;
+    const double round = p->head_dim == 128 ? 256 : 512, rows = p->sys_len + longest;
+    if (rows > (longest <= 3 * round ? 6 : mb > 60 ? 5 : 4) * round) return false;
     const double rate = p->head_dim == 128 ? 300 : 460;              // rows of a workgroup per us
-    const double one = (p->sys_len + longest) / rate, even = (sys_mean + mean) / rate * workgroups / 256,
+    const double one = rows / rate, even = (sys_mean + mean) / rate * workgroups / 256,
                  moved = workgroups * (sys_mean + mean) * row_bytes / 16.8e6;
     const double most = one > even ? (one > moved ? one : moved) : (even > moved ? even : moved);
-    const double direct_us = 6.5 + most + 1.3 * (ceil(workgroups / 256) - 1);
-    const double tiles = ceil(total_q * (double)(p->num_q_heads / p->num_kv_heads) / 32);
-    const double mb = (tiles * sys_mean + total_q * mean) * p->num_kv_heads * row_bytes / 1e6;
+    const double direct_us = 6.5 + most + (group > 1 ? 1.3 : 1.8) * (ceil(workgroups / 256) - 1);
     const double tile_us = 9.4 + mb / 8.9 + 0.34 * log2(1 + mb) + workgroups * 0.56e-3;
     return direct_us < 14 && direct_us < tile_us;
 }
