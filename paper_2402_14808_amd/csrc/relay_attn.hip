@@ -246,14 +246,19 @@ constexpr int kMinWaveTiles = 4;
 // part through many-rows items.
 constexpr int kRowsSysMinTiles = 8;
 
+// How a decode step is planned, where a first plan shows what it comes to.
+struct DecodeWay {
+    bool by_bound = false;         // for contexts as long as the bound allows, whatever the cache holds
+    bool rows_by_bound = false;    // the kind of its system items chosen so
+};
+
 // Work decomposition; a pure function of (params, total_q) so that the workspace size the
 // caller asked for and the one the launch uses always agree.  A `budget` below that size asks for
 // the fewest partials: the cut that a caller's workspace of fixed size, made for another batch, may
-// still hold (the size does not only rise with the batch).  `by_bound` plans a decode step for contexts
-// as long as the bound allows, whatever the cache holds.
+// still hold (the size does not only rise with the batch).  `way`: see DecodeWay.
 Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q_len,
                int64_t sys_base_items = 0, bool allow_rows_sys = true, size_t budget = SIZE_MAX, int num_groups = 1,
-               double sys_mean = -1, bool by_bound = false) {
+               double sys_mean = -1, DecodeWay way = {}) {
     Plan pl{};
     const bool tight = budget != SIZE_MAX;
     const bool prefill = kind == kPrefill;
@@ -308,7 +313,7 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
         // launch that the bound leads to was faster (40 requests of 28/4 heads, contexts of 37 .. 310, 19.7 against 22.3
         // us; 153 of them, 425 .. 601, 47.5 against 52.7).
         int64_t ctx_like = ctx_tiles;
-        if (!by_bound) {
+        if (!way.by_bound) {
             const int64_t held = (int64_t)p->num_blocks * p->block_size;
             const int64_t tiles = p->num_kv_heads * (held / 32 + (total_q + 1) / 2);
             const bool many_rows = pl.n_mtiles >= 4 && tiles >= 4 * (int64_t)total_q * p->num_kv_heads;
@@ -338,13 +343,13 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
         // From four row tiles (one full block of 128 rows) on it still pays when the system part
         // is both large (64 tiles per compute unit) and at least as large as the context part:
         // batch 128 of the Llama-30B shape at s = 8192 157 -> 128 us, batch 192 at 4096 163 -> 144 us.
-        {
+        auto rows_pay = [&](int64_t ctx) {
             const int64_t sys_all = base_items * sys_tiles;
-            const bool wide = pl.n_mtiles >= kRowsSysMinTiles && 2 * sys_all >= ctx_like;
-            const bool full_block = pl.n_mtiles >= 4 && sys_all >= 64 * (kWorkgroupSlots / 2) &&
-                                    sys_all >= ctx_like;
-            pl.rows_sys = allow_rows_sys && sys_base_items == 0 && p->sys_len > 0 && (wide || full_block);
-        }
+            const bool wide = pl.n_mtiles >= kRowsSysMinTiles && 2 * sys_all >= ctx;
+            const bool full_block = pl.n_mtiles >= 4 && sys_all >= 64 * (kWorkgroupSlots / 2) && sys_all >= ctx;
+            return allow_rows_sys && sys_base_items == 0 && p->sys_len > 0 && (wide || full_block);
+        };
+        pl.rows_sys = rows_pay(way.rows_by_bound ? ctx_tiles : ctx_like);
         if (pl.rows_sys) {
             const int64_t rb_items = (int64_t)p->num_kv_heads * pl.n_sys_rowblocks;
             int chunk = p->sys_chunk_tokens;
@@ -429,7 +434,7 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
                 // 21 .. 30, s = 437: 35.5 -> 21.2 us; 7 of 32 heads, 5 .. 17, s = 5429: 32.0 -> 24.2; 145 of 40 heads,
                 // 30 .. 40, s = 162: 71 -> 47; longer contexts come out as before.
                 const double t_item = (double)ctx_like / ((double)total_q * p->num_kv_heads);
-                if (!by_bound) {
+                if (!way.by_bound) {
                     const double turns = (pl.rows_sys ? 0.5 * t_sys : sys_wgs > 0 ? t_sys : t_star) + 2.5;
                     double per_wave = turns / (0.9 + 3.0 / (t_item > 1 ? t_item : 1));
                     if (per_wave < 1) per_wave = 1;
@@ -465,7 +470,7 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
                 // 94 requests of 40 heads, 10 .. 29, s = 11916 115 -> 84 us, 93 of them, 48 .. 61, s = 1604 45.8 -> 37.8,
                 // 204 of 32/8, 12 .. 24, three prompts 34.7 -> 25.6; slower where it errs (84 of 40 heads,
                 // 13 .. 42, prompts of 100 .. 153: 24.2 -> 26.6).  With contexts of 30 tiles it did: 71 -> 77.
-                if (pl.paired && t_item < 4 && !by_bound) {
+                if (pl.paired && t_item < 4 && !way.by_bound) {
                     const double step = pl.rows_sys ? (double)pl.sys_chunk / 32 : (double)ceil_div(pl.sys_chunk, 32);
                     const double n = (double)ctx_like, even = n / (double)wgs;
                     const double draw = p->head_dim == 128 ? 0.59 : 0.3, each = 1.2 + 5.0 / (t_item > 1 ? t_item : 1);
@@ -516,10 +521,23 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
             pl.ctx_wgs = (int)wgs;
         }
         finish();
+        // Many-rows items because of what the cache holds, where the bound would not have them: with chunks of 12 tiles
+        // and more, and spans short enough for half of the context wavefronts.  Their chunks take slots from the
+        // contexts, whose spans get longer for it, and a short chunk leaves little to share.  Of 40 such steps that
+        // were timed with either kind the rule takes the faster one or one within 13 %; always the many-rows kind
+        // was up to twice as slow (173 requests of 32/8 heads, contexts of 19 .. 44, s = 1363, bound 3424, spans of 22
+        // tiles: 108 us, 53 with the other kind; 84 of 32/8 heads of 64, s = 272, chunks of 5 tiles: 11.7 and 9.7), never
+        // up to 1.5 times (99 of 40 heads, contexts of 78 .. 96, s = 8655: 122 us, 83 with chunks of 46 tiles).
+        if (pl.rows_sys && !rows_pay(ctx_tiles) &&
+            (pl.sys_chunk < 12 * 32 || (int64_t)pl.ctx_t_floor * pl.ctx_wgs * 4 > 2 * ctx_like)) {
+            way.rows_by_bound = true;
+            return make_plan(p, total_q, kind, max_q_len, sys_base_items, allow_rows_sys, budget, num_groups, sys_mean, way);
+        }
         // A plan that outgrows the workspace or the static scratch takes no more than the bound's.
-        if (!by_bound && pl.bytes > (budget < kStaticScratchBytes ? budget : kStaticScratchBytes)) {
+        if (!way.by_bound && pl.bytes > (budget < kStaticScratchBytes ? budget : kStaticScratchBytes)) {
+            way.by_bound = true;
             const Plan bound = make_plan(p, total_q, kind, max_q_len, sys_base_items, allow_rows_sys, budget, num_groups,
-                                         sys_mean, true);
+                                         sys_mean, way);
             if (!bound.unsupported && bound.bytes < pl.bytes) return bound;
         }
         return pl;
@@ -994,7 +1012,7 @@ size_t relay_attn_workspace_bytes(const ra_params *p, int32_t total_q) {
     if (!blind.unsupported && blind.bytes > most) most = blind.bytes;
     // (and a workspace serves calls over a cache of another size)
     for (const bool rows_sys : {true, false}) {
-        const Plan bound = make_plan(p, total_q, kRelayDecode, 1, 0, rows_sys, SIZE_MAX, 1, -1, true);
+        const Plan bound = make_plan(p, total_q, kRelayDecode, 1, 0, rows_sys, SIZE_MAX, 1, -1, DecodeWay{true});
         if (!bound.unsupported && bound.bytes > most) most = bound.bytes;
     }
     return most;
