@@ -250,6 +250,7 @@ constexpr int kRowsSysMinTiles = 8;
 struct DecodeWay {
     bool by_bound = false;         // for contexts as long as the bound allows, whatever the cache holds
     bool rows_by_bound = false;    // the kind of its system items chosen so
+    int64_t least_turns = 0;       // turns that a streaming system workgroup should at least have
 };
 
 // Work decomposition; a pure function of (params, total_q) so that the workspace size the
@@ -332,7 +333,8 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
         // 15.4 -> 14.4 us)
         if (t_star16 < 24) t_star16 = 24;
         const int64_t t_star = (t_star16 + 15) / 16;
-        int64_t sys_wgs = 0, t_sys = 0;
+        int64_t sys_wgs = 0, t_sys = 0, few_chunks = 0;
+        const double t_item = ctx_tiles > 0 ? (double)ctx_like / ((double)total_q * p->num_kv_heads) : 0;   // tiles of a context
         // Wide grouped-query batches: with B*G stacked rows per kv head in many row tiles, every
         // 32-row streaming item would pull the system K/V of its chunk into its compute unit
         // (from L2, but what a unit can draw is capped there too: 87 us at the Llama-3-8B shape).
@@ -372,7 +374,25 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
         if (p->sys_len > 0) {
             int chunk = p->sys_chunk_tokens;
             if (chunk == 0) {
-                int64_t n_chunks = (sys_tiles * 16 + 2 * t_star16) / (4 * t_star16);   // nearest
+                auto chunks_of = [&](int64_t t16) {                     // nearest
+                    const int64_t n = (sys_tiles * 16 + 2 * t16) / (4 * t16);
+                    return n < 1 ? (int64_t)1 : n;
+                };
+                int64_t n_chunks = chunks_of(t_star16);
+                // A plan for fewer tiles than the bound's comes to shorter chunks than that one.  They are taken as far
+                // as they save a turn of the four wavefronts (25 requests of 40 heads, s = 645: four chunks of 6 tiles
+                // 15.9 us, three of 7 13.3), and no shorter than `way` says.
+                if (ctx_like < ctx_tiles) {
+                    int64_t bound16 = ((base_items * sys_tiles + ctx_tiles) * 16 + kWaveSlots - 1) / kWaveSlots;
+                    if (bound16 < 24) bound16 = 24;
+                    few_chunks = chunks_of(bound16);
+                    if (way.least_turns > 0 && n_chunks > few_chunks) {
+                        const int64_t n = chunks_of(16 * way.least_turns);
+                        n_chunks = n < few_chunks ? few_chunks : n < n_chunks ? n : n_chunks;
+                    }
+                    auto turns = [&](int64_t n) { return ((sys_tiles + n - 1) / n + 3) / 4; };
+                    while (n_chunks > few_chunks && turns(n_chunks - 1) == turns(n_chunks)) --n_chunks;
+                }
                 // At most one system workgroup per compute unit: a compute unit cannot draw more
                 // than about 1/256 of the memory bandwidth whatever it holds, so two long
                 // workgroups on one unit finish last (measured: 208 system workgroups beat 312
@@ -433,7 +453,6 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
                 // about half a turn), as long as the machine has places.  245 requests of 28/4 heads, contexts of
                 // 21 .. 30, s = 437: 35.5 -> 21.2 us; 7 of 32 heads, 5 .. 17, s = 5429: 32.0 -> 24.2; 145 of 40 heads,
                 // 30 .. 40, s = 162: 71 -> 47; longer contexts come out as before.
-                const double t_item = (double)ctx_like / ((double)total_q * p->num_kv_heads);
                 if (!way.by_bound) {
                     const double turns = (pl.rows_sys ? 0.5 * t_sys : sys_wgs > 0 ? t_sys : t_star) + 2.5;
                     double per_wave = turns / (0.9 + 3.0 / (t_item > 1 ? t_item : 1));
@@ -532,6 +551,20 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
             (pl.sys_chunk < 12 * 32 || (int64_t)pl.ctx_t_floor * pl.ctx_wgs * 4 > 2 * ctx_like)) {
             way.rows_by_bound = true;
             return make_plan(p, total_q, kind, max_q_len, sys_base_items, allow_rows_sys, budget, num_groups, sys_mean, way);
+        }
+        // Streaming chunks shorter than the bound's are no use where the launch waits for the contexts anyway: where a span
+        // of the floor, in turns of a system workgroup (as estimated above), is longer than their turns.  Longer ones leave
+        // the contexts more workgroups and more slots, and so shorter spans.  199 steps whose plan differs from the
+        // bound's, with and without this: 0.98, up to 0.61 (6 requests of 32 heads, contexts of 126 .. 855 under 40032,
+        // s = 6204: 69.7 -> 42.8 us; 6 of 52 heads, 156 .. 436, s = 768: 22.4 -> 18.9; 132 of 28/4, 9 .. 26 under 3280, s =
+        // 1716: 36.2 -> 32.4), the worst 43.3 -> 47.1 (12 of 32/8, 571 .. 3904 under 40016, three prompts up to 5994).
+        if (way.least_turns == 0 && !pl.rows_sys && pl.n_sys_chunks > few_chunks && few_chunks > 0 && p->ctx_part_tokens == 0) {
+            double span = pl.ctx_t_floor * (0.9 + 3.0 / (t_item > 1 ? t_item : 1)) - 2.5;
+            if (span < pl.ctx_t_floor) span = pl.ctx_t_floor;
+            if (span > t_sys) {
+                way.least_turns = (int64_t)ceil(span);
+                return make_plan(p, total_q, kind, max_q_len, sys_base_items, allow_rows_sys, budget, num_groups, sys_mean, way);
+            }
         }
         // A plan that outgrows the workspace or the static scratch takes no more than the bound's.
         if (!way.by_bound && pl.bytes > (budget < kStaticScratchBytes ? budget : kStaticScratchBytes)) {
