@@ -481,25 +481,6 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
                 }
                 if (wgs < least) wgs = least;
                 if (wgs < 1) wgs = 1;
-                // The rule for even units gives what a unit without a system workgroup has left over to its context
-                // wavefronts.  With short contexts the few such units can be what the launch waits for (50 requests
-                // of 40 heads, contexts of 9 .. 56 behind s = 1792, 240 system workgroups: system parts done at 17 us,
-                // the 32 other workgroups at 27).  An estimate of both sides in us (a tile's share of the memory a
-                // unit can draw; a wavefront's own 1.2 a tile and 5 a context begun) takes equal spans then:
-                // 94 requests of 40 heads, 10 .. 29, s = 11916 115 -> 84 us, 93 of them, 48 .. 61, s = 1604 45.8 -> 37.8,
-                // 204 of 32/8, 12 .. 24, three prompts 34.7 -> 25.6; slower where it errs (84 of 40 heads,
-                // 13 .. 42, prompts of 100 .. 153: 24.2 -> 26.6).  With contexts of 30 tiles it did: 71 -> 77.
-                if (pl.paired && t_item < 4 && !way.by_bound) {
-                    const double step = pl.rows_sys ? (double)pl.sys_chunk / 32 : (double)ceil_div(pl.sys_chunk, 32);
-                    const double n = (double)ctx_like, even = n / (double)wgs;
-                    const double draw = p->head_dim == 128 ? 0.59 : 0.3, each = 1.2 + 5.0 / (t_item > 1 ? t_item : 1);
-                    auto longer = [](double a, double b) { return a > b ? a : b; };
-                    const double light = longer(0, ((double)base_items * sys_tiles + n) / (kWorkgroupSlots / 2) - step);
-                    const double heavy = wgs > sys_wgs ? (n - light * (double)sys_wgs) / (double)(wgs - sys_wgs) : 0;
-                    const double by_unit = longer(longer(draw * (step + light), draw * 2 * heavy), each * longer(heavy, light) / 4);
-                    const double equal = longer(longer(draw * (step + even), draw * 2 * even), each * even / 4);
-                    if (equal < by_unit) pl.paired = false;
-                }
                 // t_est: tiles per wavefront if every context had the maximum length.  Real
                 // lengths are shorter and the spans shrink with them, down to the floor below; a
                 // floor near t_est would leave most context wavefronts without work (a batch
@@ -528,6 +509,33 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
                 if (wide > slots) slots = wide;
                 pl.n_ctx_parts = (int)slots;
                 pl.ctx_t_floor = (int)((t_max + slots - 2) / (slots - 1));
+                // The rule for even units gives what a unit without a system workgroup has left over to its context
+                // wavefronts.  With short contexts the few such units can be what the launch waits for (50 requests
+                // of 40 heads, contexts of 9 .. 56 behind s = 1792, 240 system workgroups: system parts done at 17 us,
+                // the 32 other workgroups at 27).  An estimate of both sides in us (a tile's share of the memory a
+                // unit can draw; a wavefront's own 1.2 a tile and 5 a context begun) takes equal spans then, where the
+                // even units leave the others the longer spans, or spans below the floor (a part of those
+                // wavefronts gets the floor, and the rest nothing): 76 requests of 40 heads, 11 .. 30, s = 3128 48.3 -> 31.9
+                // us, 255 of 16 of 64, six prompts 36.1 -> 25.3, 58 of 52, s = 215 23.9 -> 20.8.  By the estimate alone
+                // launches of many contexts and little else took it too: 122 of 52 heads, 14 .. 28, s = 190 31.8 -> 34.8,
+                // 84 of 40, 13 .. 42, four prompts of 100 .. 153 24.3 -> 26.6.  With contexts of 30 tiles equal spans
+                // lost as well: 71 -> 77.
+                //   Beside many-rows items, which take a tile at about half of a streaming one's time, equal spans are for
+                // plans by the cache (161 of 40 heads, s = 3558, bound 315 60.2 -> 54.1; 171, s = 2560 52.8 -> 46.4), where the
+                // bound says little of the spans; at the bound they were no better (166 of 52, s = 4759 80.7 -> 85.9).
+                if (pl.paired && t_item < 4 && !way.by_bound && pl.rows_sys) {
+                    pl.paired = 2 * ctx_like >= ctx_tiles;
+                } else if (pl.paired && t_item < 4 && !way.by_bound) {
+                    const double step = (double)ceil_div(pl.sys_chunk, 32);
+                    const double n = (double)ctx_like, even = n / (double)wgs;
+                    const double draw = p->head_dim == 128 ? 0.59 : 0.3, each = 1.2 + 5.0 / (t_item > 1 ? t_item : 1);
+                    auto longer = [](double a, double b) { return a > b ? a : b; };
+                    const double light = longer(0, ((double)base_items * sys_tiles + n) / (kWorkgroupSlots / 2) - step);
+                    const double heavy = wgs > sys_wgs ? (n - light * (double)sys_wgs) / (double)(wgs - sys_wgs) : 0;
+                    const double by_unit = longer(longer(draw * (step + light), draw * 2 * heavy), each * longer(heavy, light) / 4);
+                    const double equal = longer(longer(draw * (step + even), draw * 2 * even), each * even / 4);
+                    if ((heavy > light || heavy < 4.2 * pl.ctx_t_floor) && equal < 0.995 * by_unit) pl.paired = false;
+                }
                 // What a row is likely to take of them: the contexts as they are planned for (short ones, the tiles that
                 // are there) in spans as the device will cut them.  Counted with contexts at the bound, short
                 // ones under a wide bound seemed to take every slot, and the fusion loaded the empty ones too (225
