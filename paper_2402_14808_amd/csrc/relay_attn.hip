@@ -623,7 +623,8 @@ bool light_if_spare(int64_t sys_wgs, int64_t ctx_wgs) {
 // 3000 and some to 10000) were timed: 177 take this form, two of them at 1.04 and 1.05 of the two-launch time and
 // the others faster (one request of 32/8 heads, s = 512, 10.3 -> 6.9 us; 16 of 16 heads of 64, s = 1000, contexts up to
 // 255, 10.8 -> 7.8), and over all the choice is 1.7 % over the faster form.  The longest context is taken to be what
-// the bound and the cache allow, not what they make likely.
+// the bound and the cache allow in the estimate, and half as long again as the cache makes likely in the rounds (4
+// requests of 32 heads, s = 488, contexts of 353 .. 416 under 1072: 15.0 us in two launches, 11.1 in one).
 //   Rounds: 16 wavefronts take 256 rows (head_dim 128; 512 at 64) of a request a round, and past the second a
 // round costs 1.4 us (1 .. 2 rounds 5.3 us, 3 7.2, 4 8.8, 5 11, 6 12.3, 8 15.5).  So up to four are taken, up to six where
 // three or fewer are context (those cost more, and the two-launch form spreads a context over the machine), and
@@ -640,10 +641,10 @@ bool direct_form(const ra_params *p, int32_t total_q, int max_ctx, double sys_me
     const int group = p->num_q_heads / p->num_kv_heads;
     const double tiles = ceil(total_q * (double)group / 32);
     const double mb = (tiles * sys_mean + total_q * mean) * p->num_kv_heads * row_bytes / 1e6;
-    const double round = p->head_dim == 128 ? 256 : 512, rows = p->sys_len + longest;
-    if (rows > (longest <= 3 * round ? 6 : mb > 60 ? 5 : 4) * round) return false;
+    const double round = p->head_dim == 128 ? 256 : 512, reach = longest < 1.5 * mean ? longest : 1.5 * mean;
+    if (p->sys_len + reach > (reach <= 3 * round ? 6 : mb > 60 ? 5 : 4) * round) return false;
     const double rate = p->head_dim == 128 ? 300 : 460;              // rows of a workgroup per us
-    const double one = rows / rate, even = (sys_mean + mean) / rate * workgroups / 256,
+    const double one = (p->sys_len + longest) / rate, even = (sys_mean + mean) / rate * workgroups / 256,
                  moved = workgroups * (sys_mean + mean) * row_bytes / 16.8e6;
     const double most = one > even ? (one > moved ? one : moved) : (even > moved ? even : moved);
     const double direct_us = 6.5 + most + (group > 1 ? 1.3 : 1.8) * (ceil(workgroups / 256) - 1);

@@ -20,6 +20,8 @@ STEPS = [
     (8, 4, 4, 64, 100, 1000, 504, True),             # 7.3, 9.3
     (34, 4, 4, 64, 34, 2336, 4964, True),            # 15.6, 20.8: five rounds, but 81 MB
     (4, 32, 8, 128, 1024, 163, 34, True),            # 10.2, 12.0
+    (4, 32, 32, 128, 488, 1072, 109, True),          # 11.1, 15.0: six rounds and more by the bound only
+    (4, 8, 8, 128, 323, 784, 49, True),              # 9.1, 12.2
     # the last row of four rounds of 256 with a context of more than three, and the one behind it
     (1, 32, 32, 128, 255, 769, 49, True), (1, 32, 32, 128, 256, 769, 49, False),
     (1, 32, 32, 64, 511, 1537, 97, True), (1, 32, 32, 64, 512, 1537, 97, False),
