@@ -133,6 +133,14 @@ bool many_new_tokens(const ra_params *p, int32_t total_q) {
     return total_q >= (int64_t)kWholeMinTokens * p->batch || (p->sys_len <= 1024 && total_q >= (int64_t)4 * p->batch);
 }
 
+// What the prefixes of a call are to an average query row: the length of its system prompt, and the requests that share it
+// (negative: one prefix).  By rows and not by prefixes: several prompts are often one large application and some
+// small ones, and a prefix that no request of the step uses counts for nothing.  (60 prompt-phase calls of
+// such groups that choose another form so: 0.81 of the time by prefixes, eight of them slower, by up to 1.3.)
+struct Groups {
+    double sys_len = -1, requests = -1;
+};
+
 // How the prompt phase is cut, where the caller leaves it to the library.
 struct PromptSplit {
     bool whole;          // one launch of items that go through prompt and contexts (see `run`)
@@ -158,8 +166,8 @@ PromptSplit coarse_split(const ra_params *p, int32_t total_q) {
 // with the present item order, its choice is 1 .. 12 % over the best cut of a shape, against up to 3.5 times for
 // the fixed rule in front of it (coarse_split): 8 requests of 9 .. 75 tokens behind contexts of 300 ..
 // 4000 118 -> 67 us, 4 requests of 10 .. 100 tokens behind 500 .. 2000 132 -> 37 us.
-// Uses nothing that the workspace size is not computed from.
-PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx, int num_groups, double sys_mean) {
+// Uses what the workspace size is computed from, and `groups` for the whole form only, which needs none of it.
+PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx, const Groups &groups) {
     const int64_t G = p->num_q_heads / p->num_kv_heads, hkv = p->num_kv_heads, batch = p->batch > 0 ? p->batch : 1;
     const int64_t s = p->sys_len, base = hkv * ((total_q * G + 127) / 128);
     const double row_bytes = (double)total_q * p->num_q_heads * p->head_dim * 4;
@@ -222,7 +230,8 @@ PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx, i
     // With several prompts the requests of a block share one of them: no more meet than an average group has
     // (the workspace is sized without the groups, so they may only ever speak for the whole form, which needs none).
     const double met = mean_new > 0 ? 128.0 / G / mean_new + 1 : 1;     // requests with rows in a block
-    const double reqs_any = met < batch ? met : batch, group = ceil((double)batch / num_groups);
+    const double reqs_any = met < batch ? met : batch, group = groups.requests < 0 ? (double)batch : ceil(groups.requests);
+    const double sys_mean = groups.sys_len < 0 ? (double)s : groups.sys_len;
     const double reqs = reqs_any < group ? reqs_any : group;
     const double ctx_long = ctx_most < 2 * held / batch ? ctx_most : 2 * held / batch;
     const double walk = ceil(s / 64.0) + reqs * ceil(ctx_long / 64), walk_mean = ceil(sys_mean / 64) + reqs * (ctx / 64 + 0.5);
@@ -258,8 +267,8 @@ struct DecodeWay {
 // the fewest partials: the cut that a caller's workspace of fixed size, made for another batch, may
 // still hold (the size does not only rise with the batch).  `way`: see DecodeWay.
 Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q_len,
-               int64_t sys_base_items = 0, bool allow_rows_sys = true, size_t budget = SIZE_MAX, int num_groups = 1,
-               double sys_mean = -1, DecodeWay way = {}) {
+               int64_t sys_base_items = 0, bool allow_rows_sys = true, size_t budget = SIZE_MAX,
+               const Groups &groups = {}, DecodeWay way = {}) {
     Plan pl{};
     const bool tight = budget != SIZE_MAX;
     const bool prefill = kind == kPrefill;
@@ -558,7 +567,7 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
         if (pl.rows_sys && !rows_pay(ctx_tiles) &&
             (pl.sys_chunk < 12 * 32 || (int64_t)pl.ctx_t_floor * pl.ctx_wgs * 4 > 2 * ctx_like)) {
             way.rows_by_bound = true;
-            return make_plan(p, total_q, kind, max_q_len, sys_base_items, allow_rows_sys, budget, num_groups, sys_mean, way);
+            return make_plan(p, total_q, kind, max_q_len, sys_base_items, allow_rows_sys, budget, groups, way);
         }
         // Streaming chunks shorter than the bound's are no use where the launch waits for the contexts anyway: where a span
         // of the floor, in turns of a system workgroup (as estimated above), is longer than their turns.  Longer ones leave
@@ -571,14 +580,13 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
             if (span < pl.ctx_t_floor) span = pl.ctx_t_floor;
             if (span > t_sys) {
                 way.least_turns = (int64_t)ceil(span);
-                return make_plan(p, total_q, kind, max_q_len, sys_base_items, allow_rows_sys, budget, num_groups, sys_mean, way);
+                return make_plan(p, total_q, kind, max_q_len, sys_base_items, allow_rows_sys, budget, groups, way);
             }
         }
         // A plan that outgrows the workspace or the static scratch takes no more than the bound's.
         if (!way.by_bound && pl.bytes > (budget < kStaticScratchBytes ? budget : kStaticScratchBytes)) {
             way.by_bound = true;
-            const Plan bound = make_plan(p, total_q, kind, max_q_len, sys_base_items, allow_rows_sys, budget, num_groups,
-                                         sys_mean, way);
+            const Plan bound = make_plan(p, total_q, kind, max_q_len, sys_base_items, allow_rows_sys, budget, groups, way);
             if (!bound.unsupported && bound.bytes < pl.bytes) return bound;
         }
         return pl;
@@ -586,7 +594,7 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
 
     const bool hand_set = p->sys_chunk_tokens != 0 || p->ctx_part_tokens != 0;
     PromptSplit split{false, 0, 256};
-    if (prefill && !hand_set && !tight) split = split_prompt(p, total_q, pl.max_ctx, num_groups, sys_mean < 0 ? p->sys_len : sys_mean);
+    if (prefill && !hand_set && !tight) split = split_prompt(p, total_q, pl.max_ctx, groups);
     else if (p->sys_len > 0 || prefill) split = coarse_split(p, total_q);
     if (!prefill) split.part = 256;
     pl.whole = prefill && !hand_set && split.whole;
@@ -714,11 +722,14 @@ ra_status run(const ra_params *p, const void *q, const int32_t *cu_seqlens_q, in
     // was computed from) is used.
     // Where the workspace is smaller than either, the cut with the fewest partials may still fit it.
     const bool multi = num_prefixes > 1;
-    double sys_mean = 0;
-    for (int i = 0; i < num_prefixes; ++i) sys_mean += (double)prefixes[i].sys_len / num_prefixes;
+    Groups groups{0, 0};
+    for (int i = 0; i < num_prefixes && i < ra::kMaxPrefixes && total_q > 0; ++i) {
+        groups.sys_len += (double)prefixes[i].sys_len * ntok[i] / total_q;
+        groups.requests += (double)prefixes[i].num_requests * ntok[i] / total_q;
+    }
     Plan pl{};
     for (size_t budget : {SIZE_MAX, workspace_bytes}) {
-        pl = make_plan(p, total_q, kind, max_q_len, multi ? sys_base_items : 0, true, budget, num_prefixes, sys_mean);
+        pl = make_plan(p, total_q, kind, max_q_len, multi ? sys_base_items : 0, true, budget, multi ? groups : Groups{});
         if (multi && kind == kRelayDecode && !pl.unsupported && pl.bytes > workspace_bytes)
             pl = make_plan(p, total_q, kind, max_q_len, sys_base_items, true, workspace_bytes);
         if (multi && !pl.unsupported && pl.bytes > workspace_bytes)
@@ -758,7 +769,7 @@ ra_status run(const ra_params *p, const void *q, const int32_t *cu_seqlens_q, in
 
     // A small decode step in one launch.  (A timeline is one of the two-launch form: it is taken of the partial
     // attention, and the result is this form's all the same.)
-    const bool direct_step = !naive && !prefill && mask == 3 && direct_form(p, total_q, pl.max_ctx, sys_mean);
+    const bool direct_step = !naive && !prefill && mask == 3 && direct_form(p, total_q, pl.max_ctx, groups.sys_len);
     auto launch_direct_step = [&]() -> ra_status {
         ra::DirectArgs d{};
         d.q = static_cast<const uint16_t *>(q);
@@ -1054,7 +1065,7 @@ size_t relay_attn_workspace_bytes(const ra_params *p, int32_t total_q) {
     if (!blind.unsupported && blind.bytes > most) most = blind.bytes;
     // (and a workspace serves calls over a cache of another size)
     for (const bool rows_sys : {true, false}) {
-        const Plan bound = make_plan(p, total_q, kRelayDecode, 1, 0, rows_sys, SIZE_MAX, 1, -1, DecodeWay{true});
+        const Plan bound = make_plan(p, total_q, kRelayDecode, 1, 0, rows_sys, SIZE_MAX, {}, DecodeWay{true});
         if (!bound.unsupported && bound.bytes > most) most = bound.bytes;
     }
     return most;
