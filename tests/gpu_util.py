@@ -24,6 +24,15 @@ def _padded_sys(a, dev):
 
 
 class DeviceCase:
+    # Whether a decode step runs as two launches whatever its size (the fixture decode_form sets it): the entry
+    # point for measurements with its phases one by one, or, where there is none, the plan's own chunk set by hand.
+    two_launches = False
+
+    @classmethod
+    def keep_two_launches(cls, params):
+        if cls.two_launches and params.sys_chunk_tokens == 0:
+            params.sys_chunk_tokens = ra.relay_attn_decode_plan(params).sys_chunk_tokens
+
     def __init__(self, case, device="cuda:0", sys_layout="dense"):
         dev = torch.device(device)
         self.case = case
@@ -54,16 +63,22 @@ class DeviceCase:
         # the workspace needs no initialisation: hand over garbage that would poison any sum
         return torch.full((nbytes,), 0xFF, dtype=torch.uint8, device=self.dev)   # all NaN as fp32
 
-    def decode(self, fp32_out=True, max_context_len=None, **tuning):
+    def decode(self, fp32_out=True, max_context_len=None, num_blocks=None, **tuning):
         c = self.case
         out, lse = self._outputs(fp32_out)
         mcl = int(c.context_lens.max()) if max_context_len is None else max_context_len
         p = ra.make_params(self.q, out, self.k_sys, self.k_cache, self.block_tables,
                            batch=c.cfg.batch, softmax_scale=c.scale, max_context_len=mcl, **tuning)
+        if num_blocks is not None:
+            p.num_blocks = num_blocks                # what a cache with room to spare would say
         ws = self._workspace(p, c.cfg.batch)
         self.last_plan = ra.relay_attn_decode_plan(p)
-        ra.relay_attn_decode(p, self.q, self.k_sys, self.v_sys, self.k_cache, self.v_cache,
-                             self.block_tables, self.context_lens, out, lse, ws)
+        args = (self.q, self.k_sys, self.v_sys, self.k_cache, self.v_cache, self.block_tables, self.context_lens, out, lse, ws)
+        if self.two_launches:
+            ra.relay_attn_debug_decode_phases(p, 1, *args)
+            ra.relay_attn_debug_decode_phases(p, 2, *args)
+        else:
+            ra.relay_attn_decode(p, *args)
         torch.cuda.synchronize()
         return out.float().cpu().numpy(), lse.cpu().numpy()
 

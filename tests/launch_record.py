@@ -2,6 +2,7 @@
 what arguments, on the CPU.  relay_attn.hip is compiled with the launchers below in place of the kernel files."""
 import ctypes
 import functools
+import hashlib
 import json
 import os
 import subprocess
@@ -61,15 +62,26 @@ hipError_t launch_empty_probe(void *, int, hipStream_t) { return hipSuccess; }
 
 @functools.lru_cache(1)
 def _library():
-    with tempfile.TemporaryDirectory() as tmp:
-        src, out = os.path.join(tmp, "launchers.hip"), os.path.join(tmp, "recorded.so")
-        with open(src, "w") as f:
-            f.write(LAUNCHERS)
-        r = subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + build.FLAGS +
-                           ["-Wl,-Bsymbolic", "-I", build.CSRC, os.path.join(build.CSRC, "relay_attn.hip"), src, "-o", out],
-                           capture_output=True, text=True)
-        assert r.returncode == 0, r.stderr[-2000:]
-        lib = ctypes.CDLL(out)
+    """Built once per state of its sources and kept beside the tests, so that a machine that is handed the tree need not
+    compile anything."""
+    text = LAUNCHERS + "".join(open(os.path.join(build.CSRC, f)).read() for f in ["relay_attn.hip"] + build.HEADERS)
+    name = hashlib.sha256((text + " ".join(build.FLAGS)).encode()).hexdigest()[:16]
+    out = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_build", "launches_%s.so" % name)
+    if not os.path.exists(out):
+        os.makedirs(os.path.dirname(out), exist_ok=True)
+        with tempfile.TemporaryDirectory(dir=os.path.dirname(out)) as tmp:
+            src, new = os.path.join(tmp, "launchers.hip"), os.path.join(tmp, "recorded.so")
+            with open(src, "w") as f:
+                f.write(LAUNCHERS)
+            r = subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + build.FLAGS +
+                               ["-Wl,-Bsymbolic", "-I", build.CSRC, os.path.join(build.CSRC, "relay_attn.hip"), src, "-o", new],
+                               capture_output=True, text=True)
+            assert r.returncode == 0, r.stderr[-2000:]
+            for old in os.listdir(os.path.dirname(out)):
+                if old.startswith("launches_"):
+                    os.unlink(os.path.join(os.path.dirname(out), old))
+            os.replace(new, out)
+    lib = ctypes.CDLL(out)
     lib.take_launches.restype = ctypes.c_char_p
     lib.relay_attn_workspace_bytes.restype = ctypes.c_size_t
     return lib

@@ -82,6 +82,7 @@ SMALL = [
 ]
 
 
+@pytest.mark.usefixtures("decode_form")
 @pytest.mark.parametrize("cfg,seed,tuning", SMALL)
 def test_decode_matches_oracle_small(cfg, seed, tuning):
     _check(W.make_case(cfg, seed), tuning, layouts=("dense", "padded"))
@@ -102,6 +103,7 @@ MANY_ROWS = [
 ]
 
 
+@pytest.mark.usefixtures("decode_form")
 @pytest.mark.parametrize("cfg,seed,tuning", MANY_ROWS, ids=["c%d" % c[1] for c in MANY_ROWS])
 def test_decode_with_many_rows_system_items(cfg, seed, tuning):
     case = W.make_case(cfg, seed)
@@ -143,6 +145,7 @@ def test_llama30b_bf16_output_at_the_headline_shape():
     assert np.abs(lse - wlse).max() <= LSE_TOL
 
 
+@pytest.mark.usefixtures("decode_form")
 @pytest.mark.parametrize("b", [4, 8, 16])
 def test_speedup_grid_corner_shapes(b):
     """Corners of the (batch, context, prompt) grid of the standalone-attention experiment
@@ -162,6 +165,7 @@ def _widen_tables(case, factor):
     return replace(case, block_tables=wide)
 
 
+@pytest.mark.usefixtures("decode_form")
 @pytest.mark.parametrize("cfg,seed,factor,bound", [
     (_cfg(), 190, 16, 0),                                                    # 0: table capacity
     (_cfg(batch=37, num_q_heads=8, num_kv_heads=2, sys_len=900, ctx_hi=300), 191, 8, 0),
@@ -215,6 +219,7 @@ def test_llama3_8b_gqa_bf16_output_sampled_rows():
     assert np.abs(lse[rows[:, 0], rows[:, 1]] - wlse).max() <= LSE_TOL
 
 
+@pytest.mark.usefixtures("decode_form")
 def test_block_placement_is_bit_exact_and_poison_is_never_read():
     case = W.make_case(_cfg(num_q_heads=8, num_kv_heads=4, sys_len=200, ctx_hi=500), 120)
     assert np.isnan(case.k_cache).any() and (case.block_tables == W.POISON_BLOCK).any()
@@ -226,7 +231,7 @@ def test_block_placement_is_bit_exact_and_poison_is_never_read():
         assert np.array_equal(got, base) and np.array_equal(lse, lse0)
 
 
-def test_one_workspace_serves_calls_with_different_shapes():
+def test_one_workspace_serves_calls_with_different_shapes(decode_form):
     """A workspace holds nothing between calls: one buffer full of garbage serves calls with
     other batch sizes and prompt lengths."""
     cases = [W.make_case(_cfg(sys_len=700, batch=9, ctx_hi=300), 130),
@@ -243,6 +248,7 @@ def test_one_workspace_serves_calls_with_different_shapes():
         assert np.abs(got - want).max() <= TOL and np.abs(lse - wlse).max() <= LSE_TOL
 
 
+@pytest.mark.usefixtures("decode_form")
 def test_runs_are_bitwise_reproducible():
     case = W.make_case(_cfg(sys_len=900, ctx_hi=400, batch=9), 121)
     dc = DeviceCase(case)
@@ -251,6 +257,7 @@ def test_runs_are_bitwise_reproducible():
     assert np.array_equal(a, b) and np.array_equal(la, lb)
 
 
+@pytest.mark.usefixtures("decode_form")
 def test_request_permutation_permutes_outputs():
     case = W.make_case(_cfg(batch=6), 122)
     base, lse0 = _check(case)
@@ -262,6 +269,7 @@ def test_request_permutation_permutes_outputs():
     np.testing.assert_allclose(lse, lse0[perm], atol=1e-5, rtol=0)
 
 
+@pytest.mark.usefixtures("decode_form")
 def test_prefix_split_point_does_not_matter():
     cfg = _cfg(sys_len=320, ctx_lo=5, ctx_hi=90)
     case = W.make_case(cfg, 123)
@@ -282,6 +290,7 @@ def test_prefix_split_point_does_not_matter():
         np.testing.assert_allclose(lse, lse0, atol=1e-4, rtol=0)
 
 
+@pytest.mark.usefixtures("decode_form")
 def test_bf16_output_is_the_rounded_fp32_output():
     case = W.make_case(_cfg(sys_len=400), 124)
     dc = DeviceCase(case)
@@ -293,6 +302,7 @@ def test_bf16_output_is_the_rounded_fp32_output():
     assert (np.abs(b16 - want) <= np.maximum(TOL, ulp)).all()
 
 
+@pytest.mark.usefixtures("decode_form")
 def test_requests_without_context_and_fully_empty_rows():
     cfg = _cfg(sys_len=100)
     case = W.make_case(cfg, 125)
@@ -310,6 +320,7 @@ def test_requests_without_context_and_fully_empty_rows():
     assert np.abs(got[keep] - want[keep]).max() <= TOL
 
 
+@pytest.mark.usefixtures("decode_form")
 def test_strided_inputs_and_head_major_system_cache():
     case = W.make_case(_cfg(num_q_heads=8, num_kv_heads=4, sys_len=210), 126)
     want, _ = _oracle(case)

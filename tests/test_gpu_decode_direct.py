@@ -1,8 +1,6 @@
 """The one-launch form of a small decode step, and the two-launch form at the same sizes (which the measurement entry
 point with its phases one by one always takes): both against the oracle."""
-import os
 import re
-import subprocess
 
 import numpy as np
 import pytest
@@ -12,6 +10,7 @@ import oracle
 import paper_2402_14808_amd as ra
 import workloads as W
 from gpu_util import DeviceCase
+from test_codegen import _device_asm
 
 TOL, LSE_TOL = 2e-3, 1e-3          # as in the other parity tests: fp32 output, error about 1e-6
 
@@ -142,12 +141,7 @@ def test_large_steps_stay_two_launches():
     assert not untouched, "the two-launch form was expected (partials in the workspace)"
 
 
-def test_no_scratch_memory(tmp_path):
-    here = os.path.dirname(os.path.abspath(ra.__file__))
-    out = str(tmp_path / "d.s")
-    subprocess.run(["/opt/rocm/bin/hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-S", "--cuda-device-only",
-                    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-everything",
-                    os.path.join(here, "csrc", "decode_direct.hip"), "-o", out], check=True, capture_output=True)
-    text = open(out).read()
+def test_no_scratch_memory():
+    text = _device_asm("decode_direct")
     assert set(re.findall(r"\.vgpr_spill_count:\s*(\d+)", text)) == {"0"}
     assert set(re.findall(r"\.private_segment_fixed_size:\s*(\d+)", text)) == {"0"}

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import oracle
+import launch_record as rec
 import paper_2402_14808_amd as ra
 import workloads as W
 from gpu_util import DeviceCase, _bf16
@@ -13,7 +14,6 @@ from test_decode_plan import _params
 pytestmark = pytest.mark.gpu
 TOL = 2e-3         # as in the other parity tests: fp32 output, error about 1e-6
 LSE_TOL = 1e-3
-LATE_BYTES = 12 << 20
 
 
 def _pad_tables(case, bound):
@@ -50,15 +50,11 @@ def test_decode(B, Hq, Hkv, d, longest, bound, prompts, late):
     sizes.append(B - sum(sizes))
     groups = W.make_prefix_groups(case, 900 + B, tuple(sizes), prompts) if len(prompts) > 1 else \
         [(0, B, case.k_sys, case.v_sys)]
-    plan = ra.relay_attn_decode_plan(_params(B, Hq, Hkv, max(prompts), bound, d=d))
-    n, rows = plan.num_sys_chunks + plan.num_ctx_slots, B * Hq
-    first = 8 * (1024 // d if n > 16 and rows <= 2048 else 1)
-    print("[case] %s prompts %s chunks %d slots %d" % (cfg, prompts, plan.num_sys_chunks, plan.num_ctx_slots), flush=True)
-    if plan.compute_units == 256:
-        t_max = bound // 32
-        t_est = -(-B * Hkv * t_max // plan.num_ctx_wavefronts)         # tiles of a span at full lengths
-        likely = plan.num_sys_chunks + -(-t_max // t_est) + 1
-        assert ((min(n, first) - likely) * rows * d * 4 > LATE_BYTES) == late
+    p = _params(B, Hq, Hkv, max(prompts), bound, d=d, num_blocks=case.k_cache.shape[0])       # as the call below
+    fuse = (rec.decode_multi(p, prompts, sizes) if len(prompts) > 1 else rec.decode(p))[-1]
+    print("[case] %s prompts %s %s" % (cfg, prompts, fuse), flush=True)
+    if ra.relay_attn_decode_plan(p).compute_units == 256:
+        assert rec.late_payloads(fuse, d) == late
     dc = DeviceCase(case)
     out, lse = dc._outputs(True)
     device = [(_bf16(k, dc.dev) if len(k) else None, _bf16(v, dc.dev) if len(v) else None, at, m) for at, m, k, v in groups]

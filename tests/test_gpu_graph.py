@@ -23,7 +23,8 @@ def _say(msg):
 
 
 @pytest.mark.parametrize("cfg,seed", [
-    (W.AttnConfig("g1", 6, 8, 4, 128, 700, 20, 300), 401),
+    (W.AttnConfig("g1", 6, 8, 4, 128, 700, 20, 300), 401),              # one launch
+    (W.AttnConfig("g2", 26, 16, 4, 128, 1700, 20, 300), 403),
     (W.llama30b(2048), 402),
 ])
 def test_captured_decode_step_replays_to_the_eager_result(cfg, seed):
@@ -62,6 +63,8 @@ def test_captured_decode_step_replays_to_the_eager_result(cfg, seed):
         torch.cuda.synchronize()
         got = out.cpu().numpy()
         assert np.array_equal(got, eager) and np.array_equal(lse.cpu().numpy(), eager_lse), replay
+        untouched = bool((ws == 0xFF).all())
+        assert untouched == (cfg.name == "g1"), "the other form was expected"
     if want.ndim == 3:
         assert np.abs(eager - want).max() <= TOL
     else:

@@ -10,7 +10,9 @@ import torch
 import oracle
 import paper_2402_14808_amd as ra
 import workloads as W
+import launch_record as rec
 from gpu_util import DeviceCase, _bf16
+from test_decode_plan import _params
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-3
@@ -56,6 +58,7 @@ def _run(case, groups, **tuning):
     p = ra.make_params(dc.q, out, proto, dc.k_cache, dc.block_tables, batch=case.cfg.batch,
                        softmax_scale=case.scale, max_context_len=int(case.context_lens.max()),
                        **tuning)
+    dc.keep_two_launches(p)
     ws = dc._workspace(p, case.cfg.batch)
     ra.relay_attn_decode_multi(p, dev_groups, dc.q, dc.k_cache, dc.v_cache, dc.block_tables,
                                dc.context_lens, out, lse, ws)
@@ -76,6 +79,7 @@ CASES = [
 ]
 
 
+@pytest.mark.usefixtures("decode_form")
 @pytest.mark.parametrize("cfg,seed,sizes,lens,tuning", CASES,
                          ids=["c%d" % c[1] for c in CASES])
 def test_multi_prefix_matches_oracle(cfg, seed, sizes, lens, tuning):
@@ -90,14 +94,22 @@ def test_multi_prefix_matches_oracle(cfg, seed, sizes, lens, tuning):
     assert err <= TOL and lerr <= LSE_TOL
 
 
-def test_one_group_is_bitwise_relay_attn_decode():
-    case = W.make_case(_cfg(batch=9, sys_len=400), 309)
-    _say("one group vs relay_attn_decode, seed 309")
+@pytest.mark.parametrize("cfg,launches", [
+    (_cfg(batch=9, sys_len=400), 1),
+    (_cfg(batch=40, num_q_heads=8, num_kv_heads=2, sys_len=2000), 2),
+])
+def test_one_group_is_bitwise_relay_attn_decode(cfg, launches):
+    case = W.make_case(cfg, 309)
+    _say("one group vs relay_attn_decode, %s seed 309" % (cfg,))
+    p = _params(cfg.batch, cfg.num_q_heads, cfg.num_kv_heads, cfg.sys_len, int(case.context_lens.max()),
+                num_blocks=case.k_cache.shape[0])
+    assert len(rec.decode(p)) == launches
     a, la = DeviceCase(case).decode()
-    b, lb = _run(case, [(0, 9, case.k_sys, case.v_sys)])
+    b, lb = _run(case, [(0, cfg.batch, case.k_sys, case.v_sys)])
     assert np.array_equal(a, b) and np.array_equal(la, lb)
 
 
+@pytest.mark.usefixtures("decode_form")
 @pytest.mark.parametrize("cfg,seed,n_apps,lens", [
     (_cfg(batch=23), 320, 3, (300, 70, 520)),
     (_cfg(batch=40, num_q_heads=8, num_kv_heads=2), 321, 12, tuple(64 * (i % 5) + 33 for i in range(12))),
@@ -130,6 +142,7 @@ def test_requests_of_an_application_anywhere_in_the_batch(cfg, seed, n_apps, len
     out, lse = dc._outputs(True)
     p = ra.make_params(dc.q, out, proto, dc.k_cache, dc.block_tables, batch=cfg.batch,
                        softmax_scale=case.scale, max_context_len=int(case.context_lens.max()))
+    dc.keep_two_launches(p)
     ws = dc._workspace(p, cfg.batch)
     sid_d = torch.tensor(sys_id.tolist(), dtype=torch.int32, device=dc.dev)
     ord_d = torch.tensor(order, dtype=torch.int32, device=dc.dev)

@@ -40,6 +40,7 @@ def _draw_decode(rng):
     return cfg, tuning
 
 
+@pytest.mark.usefixtures("decode_form")
 @pytest.mark.parametrize("seed", range(7000, 7036))
 def test_random_decode_shape(seed):
     rng = np.random.Generator(np.random.PCG64(seed))
@@ -104,6 +105,7 @@ def test_random_prefill_shape(seed):
     assert np.isfinite(got).all() and err <= TOL and lerr <= LSE_TOL
 
 
+@pytest.mark.usefixtures("decode_form")
 @pytest.mark.parametrize("seed", range(7200, 7212))
 def test_random_multi_prefix_shape(seed):
     """Random groupings of a batch over up to 8 shared prefixes of random lengths (some empty)."""
@@ -136,6 +138,7 @@ def test_random_multi_prefix_shape(seed):
     p = ra.make_params(dc.q, out, proto, dc.k_cache, dc.block_tables, batch=cfg.batch,
                        softmax_scale=case.scale, max_context_len=max(1, int(case.context_lens.max())),
                        **tuning)
+    dc.keep_two_launches(p)
     ws = dc._workspace(p, cfg.batch)
     ra.relay_attn_decode_multi(p, dev_groups, dc.q, dc.k_cache, dc.v_cache, dc.block_tables,
                                dc.context_lens, out, lse, ws)

@@ -42,7 +42,10 @@ def test_decode_matches_oracle(B, H, s, bound, ctx, want):
     rows = np.array([(t, h) for t in range(B) for h in (0, H // 2, H - 1)])
     want_o, want_l, _ = oracle.decode_attention(case.q, case.k_sys, case.v_sys, case.k_cache, case.v_cache,
                                                 case.block_tables, case.context_lens, case.scale, rows=rows)
-    got, lse = DeviceCase(case).decode(max_context_len=bound)
+    dc = DeviceCase(case)
+    got, lse = dc.decode(max_context_len=bound)
+    _, q, _ = spans(dc.last_plan, int(np.maximum(1, (case.context_lens + 31) // 32).sum()) * H, 16)
+    assert dc.last_plan.compute_units != 256 or (dc.last_plan.num_light_ctx_wavefronts > 0 and q == want)
     r = (rows[:, 0], rows[:, 1])
     assert np.isfinite(got).all() and np.abs(got[r] - want_o).max() <= 2e-3 and np.abs(lse[r] - want_l).max() <= 1e-3
 
@@ -104,7 +107,9 @@ def _decode_matches_oracle(case, bound):
     print("[case] %s" % case.cfg, flush=True)
     want_o, want_l, _ = oracle.decode_attention(case.q, case.k_sys, case.v_sys, case.k_cache, case.v_cache,
                                                 case.block_tables, case.context_lens, case.scale)
-    got, lse = DeviceCase(case).decode(max_context_len=bound)
+    dc = DeviceCase(case)
+    got, lse = dc.decode(max_context_len=bound, num_blocks=1 << 20)          # the plan that the replay above checks
+    assert dc.last_plan.compute_units != 256 or dc.last_plan.num_light_ctx_wavefronts > 0
     assert np.isfinite(got).all() and np.abs(got - want_o).max() <= 2e-3 and np.abs(lse - want_l).max() <= 1e-3
 
 

@@ -48,5 +48,9 @@ def test_decode_matches_oracle(B, Hq, Hkv, d, s, bound, tiles):
     print("[case] %s" % cfg, flush=True)
     want, wlse, _ = oracle.decode_attention(case.q, case.k_sys, case.v_sys, case.k_cache, case.v_cache,
                                             case.block_tables, case.context_lens, case.scale)
-    got, lse = DeviceCase(case).decode()
+    pad = np.full((B, -(-bound // 16) - case.block_tables.shape[1]), W.POISON_BLOCK, np.int32)
+    case.block_tables = np.ascontiguousarray(np.concatenate([case.block_tables, pad], 1))
+    dc = DeviceCase(case)
+    got, lse = dc.decode(max_context_len=bound, num_blocks=1 << 20)          # the plan that is checked above
+    assert dc.last_plan.compute_units != 256 or dc.last_plan.sys_chunk_tokens == 32 * tiles
     assert np.isfinite(got).all() and np.abs(got - want).max() <= 2e-3 and np.abs(lse - wlse).max() <= 1e-3

@@ -11,7 +11,9 @@ import torch
 import oracle
 import paper_2402_14808_amd as ra
 import workloads as W
+import launch_record as rec
 from gpu_util import DeviceCase
+from test_decode_plan import _params
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-3
@@ -35,9 +37,20 @@ def _static(dc, fp32_out=True):
     return out.float().cpu().numpy(), lse.cpu().numpy()
 
 
-def test_static_scratch_entry_matches_the_workspace_entry_twice_in_a_row():
+def _launches(case):
+    c = case.cfg
+    return len(rec.decode(_params(c.batch, c.num_q_heads, c.num_kv_heads, c.sys_len, int(case.context_lens.max()),
+                                  bs=c.block_size, d=c.head_dim, num_blocks=case.k_cache.shape[0])))
+
+
+@pytest.mark.parametrize("second,launches", [
+    (W.AttnConfig("small", 5, 8, 4, 128, 300, 1, 200), 1),
+    (W.AttnConfig("smaller", 21, 16, 16, 128, 1500, 1, 200), 2),      # reads what it wrote to the scratch
+])
+def test_static_scratch_entry_matches_the_workspace_entry_twice_in_a_row(second, launches):
     big = W.make_case(W.llama30b(2048), 7001)
-    small = W.make_case(W.AttnConfig("small", 5, 8, 4, 128, 300, 1, 200), 7002)
+    small = W.make_case(second, 7002)
+    assert _launches(big) == 2 and _launches(small) == launches
     for case in (big, small):                       # the second call is the smaller one
         _say("%s seed=%d" % (case.cfg, case.seed))
         dc = DeviceCase(case)
@@ -70,15 +83,22 @@ def test_static_scratch_entry_rejects_what_does_not_fit():
     assert e.value.status == ra.binding.RA_ERR_WORKSPACE_TOO_SMALL
 
 
-def test_static_scratch_entry_under_graph_capture():
+@pytest.mark.parametrize("cfg,launches", [
+    (W.AttnConfig("cap", 7, 8, 4, 128, 300, 5, 400), 1),
+    (W.AttnConfig("cap", 24, 32, 8, 128, 3000, 5, 400), 2),
+])
+def test_static_scratch_entry_under_graph_capture(cfg, launches):
     """The callers the entry point is for: a step captured into a HIP graph (no allocation, no
     workspace to keep alive) and replayed with eager work in between; every replay equals the
     eager result of relay_attn_decode.  The scratch address is looked up by the eager call made
     before the capture."""
-    case = W.make_case(W.AttnConfig("cap", 7, 8, 4, 128, 900, 5, 400), 7003)
+    case = W.make_case(cfg, 7003)
+    assert _launches(case) == launches
     _say("%s seed=%d" % (case.cfg, case.seed))
     dc = DeviceCase(case)
     ref, rlse = dc.decode()
+    other = W.make_case(W.AttnConfig("other", 22, 16, 16, 64, 1600, 1, 50), 7004)
+    assert _launches(other) == 2
     out, lse = dc._outputs(True)
     p = ra.make_params(dc.q, out, dc.k_sys, dc.k_cache, dc.block_tables, batch=case.cfg.batch,
                        softmax_scale=case.scale, max_context_len=int(case.context_lens.max()))
@@ -97,7 +117,7 @@ def test_static_scratch_entry_under_graph_capture():
     for replay in range(3):
         out.fill_(float("nan"))
         lse.fill_(float("nan"))
-        _static(DeviceCase(W.make_case(W.AttnConfig("other", 3, 4, 4, 64, 100, 1, 50), 7004)))   # another user of the scratch
+        _static(DeviceCase(other))                                       # another user of the scratch
         torch.cuda.synchronize()
         graph.replay()
         torch.cuda.synchronize()
