@@ -85,8 +85,11 @@ typedef struct {
     int32_t head_dim;             /* 64 or 128                                           */
     int32_t sys_len;              /* s >= 0 shared system positions                      */
     int32_t block_size;           /* tokens per cache block: 8, 16, 32, ... (power of 2) */
-    int32_t num_blocks;           /* blocks in k_cache / v_cache (the prompt phase also goes by
-                                     them where it weighs how long contexts can be)      */
+    int32_t num_blocks;           /* blocks in k_cache / v_cache; also taken, with the bound, for
+                                     how long contexts can be: by the choice between one
+                                     launch and two and the work split of a decode step,
+                                     and by the forms of the prompt phase.  (The results
+                                     differ by rounding at most.)                        */
     int32_t max_blocks_per_seq;   /* row length of block_tables                          */
     int32_t max_context_len;      /* host-side upper bound on context_lens[i]; 0 means
                                      max_blocks_per_seq * block_size.  Lengths above it
@@ -149,10 +152,11 @@ ra_status relay_attn_decode(const ra_params *p,
  *   k_new, v_new   [batch] tokens x Hkv x head_dim bf16, addressed as
  *                  base + token * new_stride_token + head * new_stride_head (elements)
  * context_lens[i] already counts the new token: its key/value belong at context position
- * context_lens[i] - 1.  The wavefront that attends over the last positions of (request i, kv
- * head g) takes that position from k_new / v_new instead of the cache and writes it to
- * k_cache / v_cache on the side; nothing else in the launch reads that cache row, and whatever
- * the row held before is never read.  A request with context_lens[i] == 0 has nothing to write.
+ * context_lens[i] - 1.  Whatever attends over that position of (request i, kv head g) takes it
+ * from k_new / v_new instead of the cache (one wavefront; in the one-launch form the workgroup of
+ * each query head of g), and one wavefront writes it to k_cache / v_cache on the side; nothing in
+ * the launch reads that cache row, and whatever it held before is never read.  A request with
+ * context_lens[i] == 0 has nothing to write.
  * On return of the stream's work the caches hold the new rows (byte-exact copies).
  */
 ra_status relay_attn_decode_append(const ra_params *p,
