@@ -2,13 +2,15 @@
 // the system prompt and the request's context and writes the output row (Eq. 7 as one softmax over
 // [system ; context]; no partials, no fusion launch).
 //
-// Bound: the chain of dependent trips, not bytes (one request of 32/8 heads, s = 512, 90 positions of
+// Bound: the chain of dependent trips and then the rows, not bytes (one request of 32/8 heads, s = 512, 90 positions of
 // context moves 2.5 MB).  The two-launch form needs arguments -> lengths -> block ids -> keys/values ->
-// partials, then a second launch that reads the partials: 8 + 2.5 us for that call, 6.9 in this form (16 requests of
+// partials, then a second launch that reads the partials: 10.2 us for that call, 6.8 in this form (16 requests of
 // 16 heads of 64, s = 1000, contexts of 16 .. 255: 10.8 and 7.8).  Here the trips are arguments -> length -> block
-// ids -> keys/values (system rows do not wait for the two in the middle), and the wavefronts meet in LDS.  16
-// wavefronts hold up to 16 (head_dim 128) or 32 rows each and ask for as many again while they work: 512 rows of
-// a call at head_dim 128, 1024 at 64.  (Block ids come back behind the rows that were asked for before them, so a
+// ids -> keys/values (system rows do not wait for the two in the middle), and the wavefronts meet in LDS: 4.1 us of
+// kernel time with one row and warm inputs, 4.7 with cold ones.  A round of 256 rows (head_dim 128) adds about 1.3 and
+// 2.2: some 600 vector instructions a wavefront, four wavefronts a SIMD, are issued on the few units that have a
+// workgroup.  16 wavefronts hold up to 16 (head_dim 128) or 32 rows each and ask for as many again while they work: 512
+// rows of a call at head_dim 128, 1024 at 64.  (Block ids come back behind the rows that were asked for before them, so a
 // second batch of context rows starts when the first has landed.)  The query heads of a kv head re-read its rows, from
 // L2 where the kv head is the fastest grid index; what that and re-reading the system prompt per request costs
 // is why the form is for small calls only (see direct_form in relay_attn.hip for the line).

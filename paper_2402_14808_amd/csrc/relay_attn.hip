@@ -642,7 +642,7 @@ bool light_if_spare(int64_t sys_wgs, int64_t ctx_wgs) {
 // below the two-launch form's, and no request takes too many rounds of its workgroup.  Both forms of 306 drawn
 // steps (1 .. 64 requests and some to 256, 4 .. 52 query heads, prompts of 30 .. 3500 and some to 16000, contexts of 8 ..
 // 3000 and some to 10000) were timed: 177 take this form, two of them at 1.04 and 1.05 of the two-launch time and
-// the others faster (one request of 32/8 heads, s = 512, 10.3 -> 6.9 us; 16 of 16 heads of 64, s = 1000, contexts up to
+// the others faster (one request of 32/8 heads, s = 512, 10.2 -> 6.8 us; 16 of 16 heads of 64, s = 1000, contexts up to
 // 255, 10.8 -> 7.8), and over all the choice is 1.7 % over the faster form.  The longest context is taken to be what
 // the bound and the cache allow in the estimate, and half as long again as the cache makes likely in the rounds (4
 // requests of 32 heads, s = 488, contexts of 353 .. 416 under 1072: 15.0 us in two launches, 11.1 in one).

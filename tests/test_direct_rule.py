@@ -7,7 +7,7 @@ from test_decode_plan import _params
 
 # batch, q heads, kv heads, head_dim, prompt, bound, blocks of 16 in the cache; one launch?
 STEPS = [
-    (1, 32, 8, 128, 512, 90, 7, True),               # 6.9 us in one launch, 10.3 in two
+    (1, 32, 8, 128, 512, 90, 7, True),               # 6.8 us in one launch, 10.2 in two
     (16, 16, 16, 64, 1000, 255, 160, True),          # 7.8, 10.8
     (10, 8, 8, 128, 641, 1600, 634, False),          # 19.3, 14.8: long contexts
     (3, 32, 8, 128, 46, 1188, 225, False),           # 13.1, 11.2
