@@ -167,7 +167,7 @@ PromptSplit coarse_split(const ra_params *p, int32_t total_q) {
 // the fixed rule in front of it (coarse_split): 8 requests of 9 .. 75 tokens behind contexts of 300 ..
 // 4000 118 -> 67 us, 4 requests of 10 .. 100 tokens behind 500 .. 2000 132 -> 37 us.
 // Uses what the workspace size is computed from, and `groups` for the whole form only, which needs none of it.
-PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx, const Groups &groups) {
+PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx, const Groups &groups, bool tight) {
     const int64_t G = p->num_q_heads / p->num_kv_heads, hkv = p->num_kv_heads, batch = p->batch > 0 ? p->batch : 1;
     const int64_t s = p->sys_len, base = hkv * ((total_q * G + 127) / 128);
     const double row_bytes = (double)total_q * p->num_q_heads * p->head_dim * 4;
@@ -255,7 +255,8 @@ PromptSplit split_prompt(const ra_params *p, int32_t total_q, int32_t max_ctx, c
                                         launch_us(walk_any / 64, (s + reqs_any * ctx) / 64 * base, (double)base) + 4 + 2 * reqs_any <= best_us);
     const bool filled = held == (double)p->num_blocks * p->block_size;
     const bool known = (filled && held <= 1.5 * batch * max_ctx) || max_ctx <= 2 * mean_new;
-    const double lead = by_cut ? (known ? 1 : 1.25) : (known ? 0.9 : 1);
+    // (`tight`: a workspace too small for the cut.  The whole form needs none, so the estimates alone decide.)
+    const double lead = tight ? 1 : by_cut ? (known ? 1 : 1.25) : (known ? 0.9 : 1);
     best.whole = many_new_tokens(p, total_q) && (short_walk || whole_us <= lead * cut_us);
     if (best.whole) best.chunk = (int)((s + 127) / 128 * 128), best.part = longest;
     if (best.chunk < 128) best.chunk = 128;
@@ -273,6 +274,8 @@ struct DecodeWay {
     bool by_bound = false;         // for contexts as long as the bound allows, whatever the cache holds
     bool rows_by_bound = false;    // the kind of its system items chosen so
     int64_t least_turns = 0;       // turns that a streaming system workgroup should at least have
+    // (A workspace too small for the plan takes none of these refinements: they trade system chunks for context slots,
+    // and some of the least workspaces that were accepted did not hold the slots, 6.1 MB of 6.6.)
 };
 
 // Work decomposition; a pure function of (params, total_q) so that the workspace size the
@@ -413,7 +416,7 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
                         n_chunks = n < few_chunks ? few_chunks : n < n_chunks ? n : n_chunks;
                     }
                     auto turns = [&](int64_t n) { return ((sys_tiles + n - 1) / n + 3) / 4; };
-                    while (n_chunks > few_chunks && turns(n_chunks - 1) == turns(n_chunks)) --n_chunks;
+                    while (!tight && n_chunks > few_chunks && turns(n_chunks - 1) == turns(n_chunks)) --n_chunks;
                 }
                 // At most one system workgroup per compute unit: a compute unit cannot draw more
                 // than about 1/256 of the memory bandwidth whatever it holds, so two long
@@ -577,7 +580,7 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
         // was up to twice as slow (173 requests of 32/8 heads, contexts of 19 .. 44, s = 1363, bound 3424, spans of 22
         // tiles: 108 us, 53 with the other kind; 84 of 32/8 heads of 64, s = 272, chunks of 5 tiles: 11.7 and 9.7), never
         // up to 1.5 times (99 of 40 heads, contexts of 78 .. 96, s = 8655: 122 us, 83 with chunks of 46 tiles).
-        if (pl.rows_sys && !rows_pay(ctx_tiles) &&
+        if (!tight && pl.rows_sys && !rows_pay(ctx_tiles) &&
             (pl.sys_chunk < 12 * 32 || (int64_t)pl.ctx_t_floor * pl.ctx_wgs * 4 > 2 * ctx_like)) {
             way.rows_by_bound = true;
             return make_plan(p, total_q, kind, max_q_len, sys_base_items, allow_rows_sys, budget, groups, way);
@@ -588,7 +591,7 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
         // bound's, with and without this: 0.98, up to 0.61 (6 requests of 32 heads, contexts of 126 .. 855 under 40032,
         // s = 6204: 69.7 -> 42.8 us; 6 of 52 heads, 156 .. 436, s = 768: 22.4 -> 18.9; 132 of 28/4, 9 .. 26 under 3280, s =
         // 1716: 36.2 -> 32.4), the worst 43.3 -> 47.1 (12 of 32/8, 571 .. 3904 under 40016, three prompts up to 5994).
-        if (way.least_turns == 0 && !pl.rows_sys && pl.n_sys_chunks > few_chunks && few_chunks > 0 && p->ctx_part_tokens == 0) {
+        if (!tight && way.least_turns == 0 && !pl.rows_sys && pl.n_sys_chunks > few_chunks && few_chunks > 0 && p->ctx_part_tokens == 0) {
             double span = pl.ctx_t_floor * (0.9 + 3.0 / (t_item > 1 ? t_item : 1)) - 2.5;
             if (span < pl.ctx_t_floor) span = pl.ctx_t_floor;
             if (span > t_sys) {
@@ -607,8 +610,8 @@ Plan make_plan(const ra_params *p, int32_t total_q, PlanKind kind, int32_t max_q
 
     const bool hand_set = p->sys_chunk_tokens != 0 || p->ctx_part_tokens != 0;
     PromptSplit split{false, 0, 256};
-    if (prefill && !hand_set && !tight) split = split_prompt(p, total_q, pl.max_ctx, groups);
-    else if (p->sys_len > 0 || prefill) split = coarse_split(p, total_q);
+    if (prefill && !hand_set) split = split_prompt(p, total_q, pl.max_ctx, groups, tight);
+    if ((!prefill && p->sys_len > 0) || (prefill && (hand_set || (tight && !split.whole)))) split = coarse_split(p, total_q);
     if (!prefill) split.part = 256;
     pl.whole = prefill && !hand_set && split.whole;
     if (p->sys_len > 0) {
