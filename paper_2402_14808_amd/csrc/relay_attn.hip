@@ -738,14 +738,17 @@ ra_status run(const ra_params *p, const void *q, const int32_t *cu_seqlens_q, in
     // was computed from) is used.
     // Where the workspace is smaller than either, the cut with the fewest partials may still fit it.
     const bool multi = num_prefixes > 1;
-    Groups groups{0, 0};
+    // (There the whole prompt form, which needs no workspace, is also taken where only the mean over the prefixes is for it.)
+    Groups groups{0, 0}, by_prefix{0, (double)p->batch / (num_prefixes > 0 ? num_prefixes : 1)};
     for (int i = 0; i < num_prefixes && i < ra::kMaxPrefixes && total_q > 0; ++i) {
         groups.sys_len += (double)prefixes[i].sys_len * ntok[i] / total_q;
         groups.requests += (double)prefixes[i].num_requests * ntok[i] / total_q;
+        by_prefix.sys_len += (double)prefixes[i].sys_len / num_prefixes;
     }
     Plan pl{};
     for (size_t budget : {SIZE_MAX, workspace_bytes}) {
-        pl = make_plan(p, total_q, kind, max_q_len, multi ? sys_base_items : 0, true, budget, multi ? groups : Groups{});
+        const Groups &shared = budget == SIZE_MAX ? groups : by_prefix;
+        pl = make_plan(p, total_q, kind, max_q_len, multi ? sys_base_items : 0, true, budget, multi ? shared : Groups{});
         if (multi && kind == kRelayDecode && !pl.unsupported && pl.bytes > workspace_bytes)
             pl = make_plan(p, total_q, kind, max_q_len, sys_base_items, true, workspace_bytes);
         if (multi && !pl.unsupported && pl.bytes > workspace_bytes)

@@ -23,3 +23,11 @@ def test_prompt_phase_as_a_whole_where_the_cut_does_not_fit():
     p = _params(9, 16, 8, 701, 128, bs=128, d=64, num_blocks=9)
     assert rec.prefill(p, 972, 216, workspace=8087040)[0]["whole"]
     assert not rec.prefill(p, 972, 216)[0]["whole"]
+
+
+def test_several_prompts_as_a_whole_where_the_cut_does_not_fit():
+    """By the rows that share a prompt the cut is the shorter form, by the mean over the prompts the whole one."""
+    p = _params(12, 128, 32, 565, 17, d=64)
+    call = (p, [565, 182, 145, 9], [1, 1, 6, 4], [7, 7, 42, 28], 14)
+    assert rec.prefill_multi(*call, workspace=5591040)[0]["whole"]
+    assert not rec.prefill_multi(*call)[0]["whole"]
